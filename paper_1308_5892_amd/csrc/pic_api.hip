@@ -80,11 +80,9 @@ static void carve(Bump &A, const pic_config *cfg, std::vector<BoxHost> &bh, std:
             if (s >= cfg->n_species) continue;
             const size_t n = H.slots[s], ns = H.stage_cap[s];
             for (int c = 0; c < 2; ++c) {
-                S.buf[c].lc = A.take<uint8_t>(n);
+                S.buf[c].rec = A.take<uint8_t>(PBuf<R>::bytes(n));
                 S.buf[c].cell = A.take<int32_t>(n);
-                for (int a = 0; a < 3; ++a) S.buf[c].d[a] = A.take<R>(n);
-                for (int a = 0; a < 3; ++a) S.buf[c].u[a] = A.take<R>(n);
-                S.buf[c].id = ids ? A.take<int32_t>(n) : nullptr;
+                S.buf[c].id = ids ? A.take<int32_t>(n + PBuf<R>::kSpare) : nullptr;
             }
             S.stage.cell = A.take<int32_t>(ns);
             for (int a = 0; a < 3; ++a) S.stage.d[a] = A.take<R>(ns);
@@ -165,7 +163,7 @@ static int validate(const pic_config *cfg, std::vector<BoxHost> &bh, std::string
             if (mp < 0) { err = "negative capacity"; return PIC_EINVAL; }
             const int64_t ovf = std::max<int64_t>(1024, mp / 16);
             const int64_t slots = (int64_t)std::ceil(mp * hr) + 32 * (int64_t)H.ntiles + ovf;
-            // particle arrays are addressed with 32-bit byte offsets (8-byte elements in the FP64 form)
+            // packed cells and ids are addressed with 32-bit byte offsets
             if (slots >= (int64_t)1 << 29) { err = "more than 2^29 particle slots in one species"; return PIC_EINVAL; }
             H.slots[s] = (int32_t)slots;
             H.ovf_cap[s] = (int32_t)ovf;
@@ -250,7 +248,7 @@ struct pic_ctx {
     int bpar = 0;                           // which descriptor array holds the current b (Layout::boxes)
     int64_t step = 0;
     size_t lds_bytes = 0;
-    bool fixed444 = false;             // every tile 4x4x4: the fixed-shape push kernel
+    bool fixed444 = false;             // every tile 4x4x4 and every particle copy below 4 GiB: the fixed-shape push kernel
     bool walls = false;                // some box has conducting walls
     bool pending = false;
     uint32_t flags_seen = 0;
@@ -500,6 +498,9 @@ static int init_t(pic_ctx *ctx)
     for (auto &H : ctx->bh) {
         lds = std::max(lds, push_lds_bytes<R>(H.tile[0], H.tile[1], H.tile[2]));
         all444 = all444 && H.tile[0] == 4 && H.tile[1] == 4 && H.tile[2] == 4;
+        // the fixed-shape kernel addresses a copy's groups with 32-bit byte offsets
+        for (int s = 0; s < ctx->cfg.n_species; ++s)
+            all444 = all444 && PBuf<R>::bytes(H.slots[s]) <= UINT32_MAX;
     }
     ctx->lds_bytes = lds;
     ctx->fixed444 = all444;
@@ -859,17 +860,12 @@ static int get_particles_t(pic_ctx *ctx, int box, int s, double *x, double *u, i
     }
     const size_t ns = S.slots;
     std::vector<int32_t> cell(ns), pid(S.buf[ctx->cur].id ? ns : 0);
-    std::vector<R> dd[3], uu[3];
     const PBuf<R> &P = S.buf[ctx->cur];
-    std::vector<uint8_t> code(ns);
+    std::vector<uint8_t> rec(PBuf<R>::bytes(ns));
+    PBuf<R> H = P;                                  // the copy, in host memory
+    H.rec = rec.data();
     HIPCHK(hipMemcpyAsync(cell.data(), P.cell, ns * 4, hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(hipMemcpyAsync(code.data(), P.lc, ns, hipMemcpyDeviceToHost, ctx->stream));
-    for (int a = 0; a < 3; ++a) {
-        dd[a].resize(ns);
-        uu[a].resize(ns);
-        HIPCHK(hipMemcpyAsync(dd[a].data(), P.d[a], ns * sizeof(R), hipMemcpyDeviceToHost, ctx->stream));
-        HIPCHK(hipMemcpyAsync(uu[a].data(), P.u[a], ns * sizeof(R), hipMemcpyDeviceToHost, ctx->stream));
-    }
+    HIPCHK(hipMemcpyAsync(rec.data(), P.rec, rec.size(), hipMemcpyDeviceToHost, ctx->stream));
     if (P.id) HIPCHK(hipMemcpyAsync(pid.data(), P.id, ns * 4, hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
     // a tile's ranges hold tile-local cell codes: the packed cell is the
@@ -877,7 +873,7 @@ static int get_particles_t(pic_ctx *ctx, int box, int s, double *x, double *u, i
     for (int t = 0; t < nt; ++t) {
         int o[3];
         tile_origin(D, t, o);
-        auto decode = [&](int64_t k) { cell[k] = local_cell(D, o, code[k]); };
+        auto decode = [&](int64_t k) { cell[k] = local_cell(D, o, slot_at(H, (int)k).code()); };
         for (int k = 0; k < na[t]; ++k) decode(start[t] + k);
         const int nbv = std::max(0, std::min(nb[t], cap[t] - bs[t]));
         for (int k = 0; k < nbv; ++k) decode(start[t] + bs[t] + k);
@@ -886,9 +882,10 @@ static int get_particles_t(pic_ctx *ctx, int box, int s, double *x, double *u, i
     for (int64_t q = 0; q < total; ++q) {
         const int64_t k = order[q];
         const int c[3] = {cell_x(cell[k]), cell_y(cell[k]), cell_z(cell[k])};
+        const PSlot<R> ps = slot_at(H, (int)k);
         for (int a = 0; a < 3; ++a) {
-            if (x) x[3 * q + a] = (double)c[a] + (double)dd[a][k];
-            if (u) u[3 * q + a] = (double)uu[a][k];
+            if (x) x[3 * q + a] = (double)c[a] + (double)ps.d(a);
+            if (u) u[3 * q + a] = (double)ps.u(a);
         }
         if (id) id[q] = P.id ? pid[k] : 0;
     }

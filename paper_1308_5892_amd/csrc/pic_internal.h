@@ -56,12 +56,72 @@ __host__ __device__ inline int cell_z(int32_t c) { return (int)((uint32_t)c >> 2
 // the tile, x | y << tx | z << (tx + ty) (tile edges 2^tx, 2^ty, 2^tz, at most
 // 256 cells; tiles start at multiples of their edges, so the code is the low
 // bits of the cell's coordinates).  The overflow region, whose particles
-// belong to any tile, and the leavers a push stages for the hand-over keep the
-// packed cell.
+// belong to any tile, keeps the packed cell; so do the leavers that the push's
+// general loop stages for the hand-over (its loop for 4x4x4 tiles stages a
+// one-byte code of the tile grown by one cell).
+//
+// d, u and the code of a copy are kept in groups of slots: six rows of values
+// (d x, y, z, u x, y, z), then the codes.  A block that walks a tile's segment
+// then reads one stream and writes one, instead of seven of each: a
+// copy-shaped kernel with the push's block order moves 33.5 M particles in
+// 0.319 ms this way and in 0.384-0.424 ms with one array per value (5.3
+// against 4.0-4.4 TB/s), and a slot is one address with constant offsets.
+// 128 slots in FP32 (3200 B, whole 128-B lines); 64 in FP64 (3136 B), where the
+// rows of 128 slots would lie past a load's constant offset.
 template <typename R>
 struct PBuf {                      // one copy of the particle arrays
-    PIC_GLOBAL uint8_t *lc;        // tile-local cell code (tile ranges); nullptr in the stage
-    PIC_GLOBAL int32_t *cell;      // packed cell (overflow region, staged leavers, stage)
+    static constexpr int kSlots = sizeof(R) == 4 ? 128 : 64, kShift = sizeof(R) == 4 ? 7 : 6;
+    static constexpr int kRow = kSlots * (int)sizeof(R);
+    static constexpr int kGroup = 6 * kRow + kSlots;
+    PIC_GLOBAL uint8_t *rec;       // the groups
+    PIC_GLOBAL int32_t *cell;      // packed cell (overflow region, staged leavers)
+    PIC_GLOBAL int32_t *id;        // nullptr without PIC_TRACK_IDS
+    static constexpr int kSpare = 64;   // slots after the last one that idle lanes may write
+    __host__ __device__ static size_t bytes(size_t slots)
+    {
+        return (slots + kSpare + kSlots - 1) / kSlots * (size_t)kGroup;
+    }
+};
+
+// One slot of a copy: the address of its d x (the other five values are whole
+// rows further on) and of its code.
+template <typename R>
+struct PSlot {
+    PIC_GLOBAL uint8_t *row, *lc;
+    __host__ __device__ PIC_GLOBAL R &d(int a) const
+    {
+        return *reinterpret_cast<PIC_GLOBAL R *>(row + a * PBuf<R>::kRow);
+    }
+    __host__ __device__ PIC_GLOBAL R &u(int a) const { return d(3 + a); }
+    __host__ __device__ PIC_GLOBAL uint8_t &code() const { return *lc; }
+};
+
+// Slot i of copy P.  NARROW: the copy is smaller than 4 GiB, so that a slot is
+// a 32-bit byte offset from a (wave-uniform) base, formed with 24-bit
+// multiplies (slots / 64 < 2^23).
+template <bool NARROW = false, typename R>
+__host__ __device__ inline PSlot<R> slot_at(const PBuf<R> &P, int i)
+{
+    constexpr uint32_t G = PBuf<R>::kGroup;
+    PSlot<R> s;
+    const uint32_t l = (uint32_t)i & (PBuf<R>::kSlots - 1), g = (uint32_t)i >> PBuf<R>::kShift;
+#ifdef __HIP_DEVICE_COMPILE__
+    if (NARROW) {
+        const uint32_t at = __umul24(g, G) + l;
+        s.row = P.rec + (uint32_t)(at + l * (uint32_t)(sizeof(R) - 1));
+        s.lc = P.rec + at + 6 * PBuf<R>::kRow;
+        return s;
+    }
+#endif
+    PIC_GLOBAL uint8_t *at = P.rec + (uint64_t)g * G + l;
+    s.row = at + l * (uint32_t)(sizeof(R) - 1);
+    s.lc = at + 6 * PBuf<R>::kRow;
+    return s;
+}
+
+template <typename R>
+struct PStage {                    // particles loaded or set and not yet binned
+    PIC_GLOBAL int32_t *cell;
     PIC_GLOBAL R *d[3];
     PIC_GLOBAL R *u[3];
     PIC_GLOBAL int32_t *id;        // nullptr without PIC_TRACK_IDS
@@ -70,7 +130,7 @@ struct PBuf {                      // one copy of the particle arrays
 template <typename R>
 struct SpeciesDev {
     PBuf<R> buf[2];
-    PBuf<R> stage;                 // freshly loaded / set particles, unbinned
+    PStage<R> stage;
     PIC_GLOBAL int32_t *seg_start[2];   // ntiles + 1 per copy (last: overflow region)
     PIC_GLOBAL int32_t *seg_cap[2];     // ntiles + 1 per copy
     PIC_GLOBAL int32_t *na[2];          // ntiles + 1 per copy: A-range count

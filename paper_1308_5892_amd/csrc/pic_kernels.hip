@@ -243,9 +243,9 @@ __device__ inline int claim_slot(PIC_GLOBAL int32_t *cnt, int target, bool pendi
     return slot;
 }
 
-// Element i of a particle array as a 32-bit byte offset from the array's
-// (wave-uniform) base: slot counts stay below 2^29, so the offset fits and the
-// access is one scalar base plus one vector offset.
+// Element i of a 4-byte particle array (packed cells, ids) as a 32-bit byte
+// offset from the array's (wave-uniform) base: slot counts stay below 2^29, so
+// the offset fits and the access is one scalar base plus one vector offset.
 template <typename T>
 __device__ inline PIC_GLOBAL T &slot_ref(PIC_GLOBAL T *base, int i)
 {
@@ -256,14 +256,15 @@ __device__ inline PIC_GLOBAL T &slot_ref(PIC_GLOBAL T *base, int i)
 // Store a particle at slot `at` of copy P.  wide: the slot is in the overflow
 // region or stages a leaver, and takes the packed cell; otherwise it is in
 // the ranges of the cell's tile and takes the tile-local code.
-template <typename R>
+template <bool NARROW = false, typename R>
 __device__ inline void write_particle(const PBuf<R> &P, int at, bool wide, int32_t cell, int code, const R d[3],
                                       const R u[3], int32_t id)
 {
+    const PSlot<R> s = slot_at<NARROW>(P, at);
     if (wide) slot_ref(P.cell, at) = cell;
-    else slot_ref(P.lc, at) = (uint8_t)code;
-    slot_ref(P.d[0], at) = d[0]; slot_ref(P.d[1], at) = d[1]; slot_ref(P.d[2], at) = d[2];
-    slot_ref(P.u[0], at) = u[0]; slot_ref(P.u[1], at) = u[1]; slot_ref(P.u[2], at) = u[2];
+    else s.code() = (uint8_t)code;
+    s.d(0) = d[0]; s.d(1) = d[1]; s.d(2) = d[2];
+    s.u(0) = u[0]; s.u(1) = u[1]; s.u(2) = u[2];
     if (P.id) slot_ref(P.id, at) = id;
 }
 
@@ -569,14 +570,19 @@ __device__ inline void first_breakpoint(const R d[3], const R D[3], const int di
     }
 }
 
-// Meta word of a queued move: next piece k (bits 0-1), crossings nb (2-3),
-// the crossing axes in order o0, o1, o2 (4-9), and per axis the crossing
-// direction + 1 (10-15).
+// Meta word of a queued move: per axis a the crossing direction + 1 (bits 8a,
+// 8a + 1), next piece k (bits 2-3), crossings nb (4-5) and the crossing axes
+// in order o0, o1, o2 (10-15).
+constexpr int kMetaK = 2, kMetaNb = 4, kMetaO = 10;
 __device__ inline int move_meta(int k, int nb, int o0, int o1, int o2, const int dir[3])
 {
-    return k | (nb << 2) | (o0 << 4) | (o1 << 6) | (o2 << 8) | ((dir[0] + 1) << 10) | ((dir[1] + 1) << 12) |
-           ((dir[2] + 1) << 14);
+    return (k << kMetaK) | (nb << kMetaNb) | (o0 << kMetaO) | (o1 << (kMetaO + 2)) | (o2 << (kMetaO + 4)) |
+           (dir[0] + 1) | ((dir[1] + 1) << 8) | ((dir[2] + 1) << 16);
 }
+__device__ inline int meta_k(int meta) { return (meta >> kMetaK) & 3; }
+__device__ inline int meta_nb(int meta) { return (meta >> kMetaNb) & 3; }
+__device__ inline int meta_axis(int meta, int i) { return (meta >> (kMetaO + 2 * i)) & 3; }
+__device__ inline int meta_dir(int meta, int a) { return ((meta >> (8 * a)) & 3) - 1; }
 
 // Piece k of a queued move (0 <= k <= nb crossings), from its start ps (the
 // previous breakpoint; home-cell frame) towards the move's end x1.  The piece
@@ -593,17 +599,17 @@ template <typename R>
 __device__ inline void chain_piece(const R ps[3], const R x1[3], int meta, int k, R pe[3], int offc[3], R sv[3],
                                    R dd[3])
 {
-    const int nb = (meta >> 2) & 3;
+    const int nb = meta_nb(meta);
     int crossed = 0;
-    if (k > 0) crossed |= 1 << ((meta >> 4) & 3);
-    if (k > 1) crossed |= 1 << ((meta >> 6) & 3);
-    if (k > 2) crossed |= 1 << ((meta >> 8) & 3);
+    if (k > 0) crossed |= 1 << meta_axis(meta, 0);
+    if (k > 1) crossed |= 1 << meta_axis(meta, 1);
+    if (k > 2) crossed |= 1 << meta_axis(meta, 2);
 #pragma unroll
-    for (int a = 0; a < 3; ++a) offc[a] = (crossed >> a) & 1 ? ((meta >> (10 + 2 * a)) & 3) - 1 : 0;
+    for (int a = 0; a < 3; ++a) offc[a] = (crossed >> a) & 1 ? meta_dir(meta, a) : 0;
     if (k < nb) {
-        const int ax = (meta >> (4 + 2 * k)) & 3;
+        const int ax = meta_axis(meta, k);
         const R Dp[3] = {x1[0] - ps[0], x1[1] - ps[1], x1[2] - ps[2]};
-        const R plane = ((meta >> (10 + 2 * ax)) & 3) == 2 ? R(1) : R(0);
+        const R plane = meta_dir(meta, ax) > 0 ? R(1) : R(0);
         // the parameter of the crossing along the rest of the move; a rest
         // that no longer moves along the axis (0 * inf) gives 0
         R l = (plane - sel3(ax, ps[0], ps[1], ps[2])) * fast_rcp(sel3(ax, Dp[0], Dp[1], Dp[2]));
@@ -630,7 +636,7 @@ __device__ inline void chain_piece(const R ps[3], const R x1[3], int meta, int k
 template <typename R, typename Add>
 __device__ inline void deposit_chain(const R ps0[3], const R x1[3], int meta, int k, R scale, Add &&add)
 {
-    const int nb = (meta >> 2) & 3;
+    const int nb = meta_nb(meta);
     R ps[3] = {ps0[0], ps0[1], ps0[2]};
     for (; k <= nb; ++k) {
         R pe[3], sv[3], dd[3];
@@ -682,7 +688,7 @@ __device__ inline void deposit_move(const R d[3], const R D[3], R scale, Add &&a
     R x1[3], lam[3], l0;
     int dir[3], o0;
     const int meta = move_order(d, D, 1, x1, dir, lam, o0, l0);
-    const int nb = (meta >> 2) & 3;
+    const int nb = meta_nb(meta);
     R p1[3];
     if (nb == 0) {
         p1[0] = x1[0]; p1[1] = x1[1]; p1[2] = x1[2];
@@ -795,6 +801,61 @@ __device__ inline int move_bin(const TileGeom<R> &g, const TileRim &rim, const i
     return bad ? -1 : code;
 }
 
+// Cell coordinates of a 4x4x4 tile as bytes of one word (axis a in byte a), so
+// that one instruction works on the three axes: the dot product with byte
+// weights turns them into a table index, and adding a packed move shifts all
+// three.  A moved particle's coordinate c lies in [-1, ext]; its word P holds
+// c + 4 per byte.
+__device__ inline uint32_t udot4(uint32_t a, uint32_t b) { return __builtin_amdgcn_udot4(a, b, 0u, false); }
+constexpr uint32_t kOnes = 0x010101u, kThrees = 0x030303u, kFours = 0x040404u;
+
+// Where the moved particles of a tile go: per axis t = 0, 1 or 2 (the tile
+// below, the same, the tile above) and q, the coordinate in that tile.  In a
+// regular tile (4x4x4, full tiles around it, more than one tile per axis)
+// these are the bits of P; in a partial tile, at the box's lower edge when its
+// last tile is partial, or on an axis that one tile spans, the axis decides.
+struct TileMove {
+    bool regular;
+    int ext[3], low[3];              // cells of the tile; coordinate of cell -1 in its tile
+    bool span[3];
+    template <typename R>
+    __device__ void init(const BoxDev<R> &B, const TileGeom<R> &g)
+    {
+        regular = true;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            ext[a] = g.ext[a];
+            span[a] = B.ntile[a] == 1;
+            low[a] = g.o[a] == 0 ? (B.n[a] - 1) & 3 : 3;
+            regular = regular && ext[a] == 4 && !span[a] && low[a] == 3;
+        }
+    }
+    __device__ void to(uint32_t P, uint32_t &t, uint32_t &q) const
+    {
+        if (regular) {
+            t = (P >> 2) & kThrees;
+            q = P & kThrees;
+            return;
+        }
+        t = q = 0u;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const int c = (int)((P >> (8 * a)) & 255u) - 4;
+            const bool up = c == ext[a], dn = c < 0;
+            t |= (uint32_t)(span[a] ? 1 : (up ? 2 : (dn ? 0 : 1))) << (8 * a);
+            q |= (uint32_t)(up ? 0 : (dn ? low[a] : c)) << (8 * a);
+        }
+    }
+};
+// A staged leaver's byte: c + 1 of the three axes in base 6 (the tile grown by
+// one cell, 216 codes), and back (exact for every code below 216).
+__device__ inline uint32_t leaver_code(uint32_t P) { return udot4(P, 0x240601u) - 3u * 43u; }
+__device__ inline uint32_t leaver_cell(uint32_t c)
+{
+    const uint32_t z = (c * 57u) >> 11, r = c - 36u * z, y = (r * 43u) >> 8, x = r - 6u * y;
+    return (x | (y << 8) | (z << 16)) + kThrees;
+}
+
 template <typename R> struct PushWaves { static constexpr int value = 4; };
 template <> struct PushWaves<double> { static constexpr int value = 3; };
 
@@ -824,7 +885,8 @@ __device__ void push_overflow(const BoxDev<R> &B, int kblk, const StepConst<R> &
             R d[3] = {R(0.5), R(0.5), R(0.5)}, u[3] = {R(0), R(0), R(0)};
             if (valid) {
                 cell = P.cell[idx];
-                for (int a = 0; a < 3; ++a) { d[a] = P.d[a][idx]; u[a] = P.u[a][idx]; }
+                const PSlot<R> ps = slot_at(P, idx);
+                for (int a = 0; a < 3; ++a) { d[a] = ps.d(a); u[a] = ps.u(a); }
                 if (P.id) id = P.id[idx];
             }
             const int ix = cell_x(cell), iy = cell_y(cell), iz = cell_z(cell);
@@ -889,6 +951,14 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
     const int tid = threadIdx.x;
     const TileGeom<R> g = tile_geom<R, FIX>(B, T);
     const TileRim rim = tile_rim(B, g);
+    // 4x4x4 tiles take the packed loop, except those on a conducting wall
+    bool packed = FIX != 0;
+    if (WALLS) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) packed = packed && !(B.wall == a && (g.o[a] == 0 || g.o[a] + g.ext[a] == B.n[a]));
+    }
+    TileMove mv;
+    mv.init(B, g);
     // per axis: box edge length, whether the tile touches the box edge (only
     // then can a move wrap), and whether one tile spans the box
     int bn[3];
@@ -920,7 +990,7 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
     // re-binning counters: per species the stayers (from the front of the
     // tile's new A range), the leavers (staged from the back) and the leavers
     // per neighbour direction
-    __shared__ int sh_front[kMaxSpecies], sh_back[kMaxSpecies];
+    __shared__ int sh_cnt[2][kMaxSpecies];        // [0] stayers, [1] leavers
     __shared__ int sh_bin[kMaxSpecies][27], sh_base[kMaxSpecies][27];
     // hand-over targets per (species, direction): first slot of the claimed
     // part of the target tile's segment, and the segment's end
@@ -933,10 +1003,7 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
     // segment start in copy cur^1, read here, while the fields are staged,
     // instead of at the start of each species' loop and in the hand-over
     __shared__ int sh_rng[kMaxSpecies][5];
-    if (tid < kMaxSpecies) {
-        sh_front[tid] = 0;
-        sh_back[tid] = 0;
-    }
+    if (tid < 2 * kMaxSpecies) (&sh_cnt[0][0])[tid] = 0;
     if (tid < kMaxSpecies * 27) (&sh_bin[0][0])[tid] = 0;
     if (tid < C.nsp) {
         const TileRanges r = tile_ranges(B.sp[tid], C.cur, T);
@@ -992,9 +1059,10 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
     R nx_d[3] = {R(0.5), R(0.5), R(0.5)}, nx_u[3] = {R(0), R(0), R(0)};
     auto fetch_particle = [&](const PBuf<R> &P, const TileRanges &src, int q) {
         const int at = src.slot(min(q, src.n - 1));
-        nx_code = slot_ref(P.lc, at);
-        nx_d[0] = slot_ref(P.d[0], at); nx_d[1] = slot_ref(P.d[1], at); nx_d[2] = slot_ref(P.d[2], at);
-        nx_u[0] = slot_ref(P.u[0], at); nx_u[1] = slot_ref(P.u[1], at); nx_u[2] = slot_ref(P.u[2], at);
+        const PSlot<R> ps = slot_at<FIX != 0>(P, at);
+        nx_code = ps.code();
+        nx_d[0] = ps.d(0); nx_d[1] = ps.d(1); nx_d[2] = ps.d(2);
+        nx_u[0] = ps.u(0); nx_u[1] = ps.u(1); nx_u[2] = ps.u(2);
         if (P.id) nx_id = slot_ref(P.id, at);
     };
     auto ranges = [&](int s) {
@@ -1005,10 +1073,14 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
         r.n = __builtin_amdgcn_readfirstlane(sh_rng[s][3]);
         return r;
     };
-    {
-        const TileRanges r0 = ranges(0);
-        if (r0.n > 0) fetch_particle(B.sp[0].buf[C.cur], r0, tid);
-    }
+    // the next species after s that has particles in the tile, C.nsp if none
+    auto next_species = [&](int s) {
+        do ++s;
+        while (s < C.nsp && __builtin_amdgcn_readfirstlane(sh_rng[s][3]) <= 0);
+        return s;
+    };
+    const int s0 = next_species(-1);
+    if (s0 < C.nsp) fetch_particle(B.sp[s0].buf[C.cur], ranges(s0), tid);
 
     // 2. b^t = b^{t-dt/2} - (dt/2) curl e^t (App. A.3.1 item 1), in place;
     //    and for the tile's own cells the full step b^{t+dt/2} = b^{t-dt/2} -
@@ -1176,7 +1248,7 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const int k = meta & 3, nb = (meta >> 2) & 3;
+        const int k = meta_k(meta), nb = meta_nb(meta);
         bool more = false;
         R pe[3] = {x1[0], x1[1], x1[2]};
         if (lane < nq) {
@@ -1188,8 +1260,155 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
             deposit_piece<R>(jl, cb, joff, sv, dd, sc);
             more = k < nb;
         }
-        put(more, w, meta + 1, pe, x1);
+        put(more, w, meta + (1 << kMetaK), pe, x1);
     };
+    // Particle loop of 4x4x4 tiles.  What bounds it: on the 64^3 thermal box
+    // (33.5 M particles) the vector ALU, the LDS and HBM are each busy for
+    // 0.67-0.75 of the launch, so it is written for few instructions and for
+    // no wait that the data does not force (0.540 ms with the general loop,
+    // 0.510 ms with this one; 430 -> 376 VALU instructions per 64 particles):
+    // - cells, moves and bins are packed words (TileMove), every particle of
+    //   the tile's ranges goes to the tile or to one next to it, and no lane
+    //   takes a path of its own;
+    // - every iteration issues the same loads and stores, none behind a branch
+    //   (idle lanes store to the buffer's spare slots): the wait for the next
+    //   particle's loads then leaves this iteration's stores in flight.  Behind
+    //   a branch the compiler has to wait for all of them;
+    // - the buffers' addresses and the species' constants are read where the
+    //   species changes, and the first particles of the next species are
+    //   loaded one iteration ahead like any others.
+    auto packed_loop = [&]() {
+        int s = s0;
+        if (s >= C.nsp) return;
+        TileRanges src = ranges(s), nsrc = src;
+        PBuf<R> P = B.sp[s].buf[C.cur], Q = B.sp[s].buf[C.cur ^ 1];
+        R hk = R(0.5) * C.kq[s] * C.dt, scale = -C.qs[s] * qscale_bits<R>();
+        int dst_start = __builtin_amdgcn_readfirstlane(sh_rng[s][4]), spare = B.sp[s].slots;
+        const R dt = C.dt;
+        // the first particles are waited for here: a wait at the loop's top
+        // that also covers the entry could not leave stores in flight
+#pragma unroll
+        for (int a = 0; a < 3; ++a) asm volatile("" : "+v"(nx_d[a]), "+v"(nx_u[a]));
+        asm volatile("" : "+v"(nx_code), "+v"(nx_id));
+        for (int pb = 0;;) {
+            const bool valid = pb + tid < src.n;
+            const uint32_t code = (uint32_t)nx_code & 63u;
+            const int id = nx_id;
+            const R d[3] = {nx_d[0], nx_d[1], nx_d[2]};
+            R u[3] = {nx_u[0], nx_u[1], nx_u[2]};
+            int ns = s, npb = pb + kBlock;
+            if (npb >= src.n) {
+                ns = next_species(s);
+                npb = 0;
+                if (ns < C.nsp) {
+                    nsrc = ranges(ns);
+                    P = B.sp[ns].buf[C.cur];
+                }
+            }
+            // past the last chunk every lane reloads the last particle
+            fetch_particle(P, nsrc, ns < C.nsp ? npb + tid : nsrc.n);
+
+            // gather, Boris step, move
+            const uint32_t pc = __umul24(code, 0x1041u) & kThrees;
+            const R *cf = coef + __umul24(kCoef, code);
+            R E[3], Bf[3], D[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) E[c] = trilinear_eval(cf + 8 * c, d);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) Bf[c] = trilinear_eval(cf + 24 + 8 * c, d);
+            boris_move(hk, E, Bf, u, dt, valid, C.flags, D);
+
+            // node planes crossed (move_crossings): floor of the end is the
+            // crossing direction, its positive part the plane
+            R x1[3], fl[3], pl[3], lam[3];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                x1[a] = d[a] + D[a];
+                fl[a] = floor(x1[a]);
+                pl[a] = clamp01(fl[a]);
+                lam[a] = fl[a] != R(0) ? (pl[a] - d[a]) * fast_rcp(D[a]) : R(2);
+            }
+            const int F = (int)fma(fl[2], R(65536), fma(fl[1], R(256), fl[0]));
+            const bool cross = F != 0;
+            const uint32_t Pw = pc + kFours + (uint32_t)F;
+            uint32_t t, q;
+            mv.to(Pw, t, q);
+
+            // re-binning: lanes 0 and 1 claim the wave's stayer and leaver slots
+            const bool stay = valid && t == kOnes, lv = valid && t != kOnes;
+            const uint64_t ms = __ballot(stay), ml = __ballot(lv);
+            int claimed = 0;
+            if (lane < 2) claimed = atomicAdd(&sh_cnt[lane][s], lane ? (int)__popcll(ml) : (int)__popcll(ms));
+            if (lv) atomicAdd(&sh_bin[s][udot4(t, 0x090301u)], 1);
+
+            // deposit: the first piece at once, the rest of the move queued;
+            // the crossings in (stable) increasing order of their parameter
+            const bool c10 = lam[1] < lam[0], c20 = lam[2] < lam[0], c21 = lam[2] < lam[1];
+            const bool f2 = c20 && c21;
+            const R l0 = f2 ? lam[2] : (c10 ? lam[1] : lam[0]);
+            const int jb = (int)udot4(pc, 1u | (7u << 8) | (49u << 16)) + 57;
+            R p1[3] = {x1[0], x1[1], x1[2]};
+            if (cross) {
+                const R q0 = clamp01(fma(l0, D[0], d[0])), q1 = clamp01(fma(l0, D[1], d[1])),
+                        q2 = clamp01(fma(l0, D[2], d[2]));
+                p1[0] = f2 || c10 ? q0 : pl[0];
+                p1[1] = !f2 && c10 ? pl[1] : q1;
+                p1[2] = f2 ? pl[2] : q2;
+            }
+            if (valid) {
+                const R dd[3] = {p1[0] - d[0], p1[1] - d[1], p1[2] - d[2]};
+                deposit_piece<R>(jl, jb, joff, d, dd, scale);
+            }
+
+            // store: stayers from the front of the tile's segment, leavers from
+            // the back of its first n slots, idle lanes to the spare slots
+            {
+                const int fb = dst_start + __builtin_amdgcn_readlane(claimed, 0);
+                const int bb = dst_start + src.n - 1 - __builtin_amdgcn_readlane(claimed, 1);
+                int at = stay ? fb + lane_rank(ms) : bb - lane_rank(ml);
+                at = valid ? at : spare + lane;
+                const PSlot<R> ps = slot_at<true>(Q, at);
+                ps.code() = (uint8_t)(stay ? udot4(q, 0x100401u) : leaver_code(Pw));
+#pragma unroll
+                for (int a = 0; a < 3; ++a) ps.d(a) = offset_in_cell(x1[a]);
+#pragma unroll
+                for (int a = 0; a < 3; ++a) ps.u(a) = u[a];
+                if (Q.id) slot_ref(Q.id, at) = id;
+            }
+
+            if (kQCap < 128) {
+                const int cnt = (int)__popcll(__ballot(valid && cross));
+                while (qcount + cnt > kQCap) drain();
+            }
+            {
+                const uint32_t Fw = kOnes + (uint32_t)F;
+                const int nb = 3 - __popc(Fw & kOnes);
+                const int o012 = c10 ? (c20 ? (c21 ? 2 | (1 << 2) : 1 | (2 << 2)) | (0 << 4) : 1 | (2 << 4))
+                                     : (c21 ? (c20 ? 2 | (1 << 4) : (2 << 2) | (1 << 4)) : (1 << 2) | (2 << 4));
+                put(valid && cross, scale < R(0) ? (int)((uint32_t)jb | 0x80000000u) : jb,
+                    (int)Fw | (1 << kMetaK) | (nb << kMetaNb) | (o012 << kMetaO), p1, x1);
+            }
+            while (qcount >= 64) drain();
+
+            if (ns >= C.nsp) break;
+            if (ns != s) {
+                s = ns;
+                src = nsrc;
+                Q = B.sp[s].buf[C.cur ^ 1];
+                hk = R(0.5) * C.kq[s] * C.dt;
+                scale = -C.qs[s] * qscale_bits<R>();
+                dst_start = __builtin_amdgcn_readfirstlane(sh_rng[s][4]);
+                spare = B.sp[s].slots;
+            }
+            pb = npb;
+        }
+    };
+    if constexpr (FIX != 0) {
+        if (packed) packed_loop();
+    }
+    // the general loop: other tile shapes, tiles on a conducting wall
+    if constexpr (FIX == 0 || WALLS != 0)
+    if (!packed)
     for (int s = 0; s < C.nsp; ++s) {
         const SpeciesDev<R> &S = B.sp[s];
         const PBuf<R> &P = S.buf[C.cur];
@@ -1202,7 +1421,7 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
         const int dst_start = __builtin_amdgcn_readfirstlane(sh_rng[s][4]);
         const int ovf0 = S.slots - S.ovf_cap;           // first slot of the overflow region
         auto fetch = [&](int q) { fetch_particle(P, src, q); };
-        if (n > 0 && s > 0) fetch(tid);                  // species 0: loaded during the set-up
+        if (n > 0 && s != s0) fetch(tid);                // the first species: loaded during the set-up
         for (int pb = 0; pb < n; pb += kBlock) {
             const int p = pb + tid;
             const bool valid = p < n;
@@ -1297,8 +1516,8 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
             const int sl = ms ? __ffsll((unsigned long long)ms) - 1 : 0;
             const int ll = ml ? __ffsll((unsigned long long)ml) - 1 : 0;
             int fb = 0, bb = 0;
-            if (stay && lane == sl) fb = atomicAdd(&sh_front[s], (int)__popcll(ms));
-            if (lv && lane == ll) bb = atomicAdd(&sh_back[s], (int)__popcll(ml));
+            if (stay && lane == sl) fb = atomicAdd(&sh_cnt[0][s], (int)__popcll(ms));
+            if (lv && lane == ll) bb = atomicAdd(&sh_cnt[1][s], (int)__popcll(ml));
             if (lv) atomicAdd(&sh_bin[s][bin], 1);
             fb = __builtin_amdgcn_readlane(fb, sl);
             bb = __builtin_amdgcn_readlane(bb, ll);
@@ -1311,7 +1530,7 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
                 const int slot = atomicAdd(&S.nb[dst][tn], 1);
                 at = b_range_slot(B, S, dst, tn, S.bs[dst][tn] + slot, C.flags);
             }
-            if (at >= 0) write_particle(S.buf[dst], at, lv || at >= ovf0, ncell, ncode, dn, u, id);
+            if (at >= 0) write_particle<FIX != 0>(S.buf[dst], at, lv || at >= ovf0, ncell, ncode, dn, u, id);
 
             // deposit: the first piece (in the home cell) at once, the move
             // into the wave's queue for its later pieces; the crossings in
@@ -1406,11 +1625,11 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
     }
     if (tid < C.nsp) {
         const SpeciesDev<R> &S = B.sp[tid];
-        S.na[dst][T] = sh_front[tid];
+        S.na[dst][T] = sh_cnt[0][tid];
         // staged leavers of species tid: slots [first, first + nl) of copy cur^1
-        const int nl = sh_back[tid];
+        const int nl = sh_cnt[1][tid];
         int before = 0;                                       // leavers of the species before it
-        for (int s = 0; s < tid; ++s) before += sh_back[s];
+        for (int s = 0; s < tid; ++s) before += sh_cnt[1][s];
         sh_q[tid] = S.buf[dst];
         sh_loff[tid] = sh_rng[tid][4] + sh_rng[tid][3] - nl - before;
         sh_lend[tid] = before + nl;
@@ -1436,11 +1655,13 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
                 for (int r = 0; r + 1 < kMaxSpecies; ++r) s += (r + 1 < C.nsp && q >= sh_lend[r]) ? 1 : 0;
                 const PBuf<R> &Q = sh_q[s];
                 const int from = q + sh_loff[s];
-                hcell[h] = slot_ref(Q.cell, from);
+                const PSlot<R> ps = slot_at<FIX != 0>(Q, from);
+                if (FIX && (!WALLS || packed)) hcell[h] = ps.code();
+                else hcell[h] = slot_ref(Q.cell, from);
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
-                    hd[h][a] = slot_ref(Q.d[a], from);
-                    hu[h][a] = slot_ref(Q.u[a], from);
+                    hd[h][a] = ps.d(a);
+                    hu[h][a] = ps.u(a);
                 }
                 hid[h] = Q.id ? slot_ref(Q.id, from) : 0;
                 hsp[h] = s;
@@ -1483,14 +1704,29 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
         for (int h = 0; h < kHand; ++h) {
             const int s = hsp[h];
             if (s < 0) continue;
-            const int c3[3] = {cell_x(hcell[h]), cell_y(hcell[h]), cell_z(hcell[h])};
-            const int k = move_bin(g, rim, c3);         // the same bin as at staging
+            // the same bin as at staging, and the code in the new tile
+            int k, code;
+            if (FIX && (!WALLS || packed)) {
+                uint32_t t, q;
+                mv.to(leaver_cell((uint32_t)hcell[h]), t, q);
+                k = (int)udot4(t, 0x090301u);
+                code = (int)udot4(q, 0x100401u);
+            } else {
+                const int c3[3] = {cell_x(hcell[h]), cell_y(hcell[h]), cell_z(hcell[h])};
+                k = move_bin(g, rim, c3);
+                code = local_code(B, hcell[h]);
+            }
             const int pos = sh_base[s][k] + atomicAdd(&sh_bin[s][k], 1);
             const bool wide = pos >= sh_tend[s][k];
             int at;
             if (!wide) {
                 at = sh_tseg[s][k] + pos;
             } else {                                    // the target segment is full: overflow region
+                if (FIX && (!WALLS || packed)) {        // its particles keep the packed cell
+                    int o[3];
+                    tile_origin(B, neighbor_tile(B, g, k), o);
+                    hcell[h] = pack_cell(o[0] + (code & 3), o[1] + ((code >> 2) & 3), o[2] + (code >> 4));
+                }
                 const SpeciesDev<R> &S = B.sp[s];
                 const int o = atomicAdd(&S.nb[dst][B.ntiles], 1);
                 if (o >= S.ovf_cap) {
@@ -1500,7 +1736,7 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
                     at = S.seg_start[dst][B.ntiles] + o;
                 }
             }
-            if (at >= 0) write_particle(sh_q[s], at, wide, hcell[h], local_code(B, hcell[h]), hd[h], hu[h], hid[h]);
+            if (at >= 0) write_particle<FIX != 0>(sh_q[s], at, wide, hcell[h], code, hd[h], hu[h], hid[h]);
         }
     }
 }
@@ -1856,8 +2092,9 @@ __global__ void __launch_bounds__(kBlock) repack_scatter_kernel(const BoxDev<R> 
             R d[3] = {R(0), R(0), R(0)}, u[3] = {R(0), R(0), R(0)};
             if (valid) {
                 const int idx = r.slot(p);
-                cell = it.tile >= 0 ? local_cell(B, o, P.lc[idx]) : P.cell[idx];
-                for (int a = 0; a < 3; ++a) { d[a] = P.d[a][idx]; u[a] = P.u[a][idx]; }
+                const PSlot<R> ps = slot_at(P, idx);
+                cell = it.tile >= 0 ? local_cell(B, o, ps.code()) : P.cell[idx];
+                for (int a = 0; a < 3; ++a) { d[a] = ps.d(a); u[a] = ps.u(a); }
                 if (P.id) id = P.id[idx];
             }
             store_particle(B, S, cur ^ 1, tile_of(B, cell), valid, cell, d, u, id, (PIC_GLOBAL uint32_t *)flags);
@@ -1975,9 +2212,10 @@ __global__ void __launch_bounds__(kBlock) diag_particles_kernel(const BoxDev<R> 
         double acc[6] = {0, 0, 0, 0, 0, 0};
         for (int p = first; p < r.n; p += stride) {
             const int idx = r.slot(p);
-            const int32_t cell = in_tile ? local_cell(B, g.o, P.lc[idx]) : P.cell[idx];
+            const PSlot<R> ps = slot_at(P, idx);
+            const int32_t cell = in_tile ? local_cell(B, g.o, ps.code()) : P.cell[idx];
             const int ix = cell_x(cell), iy = cell_y(cell), iz = cell_z(cell);
-            R d[3] = {P.d[0][idx], P.d[1][idx], P.d[2][idx]};
+            R d[3] = {ps.d(0), ps.d(1), ps.d(2)};
             R E[3];
             int nb = 0;
             if (in_tile) {
@@ -1998,7 +2236,7 @@ __global__ void __launch_bounds__(kBlock) diag_particles_kernel(const BoxDev<R> 
             }
             double um[3];
             for (int a = 0; a < 3; ++a)
-                um[a] = (double)P.u[a][idx] + 0.5 * (double)C.kq[s] * (double)C.dt * (double)E[a];
+                um[a] = (double)ps.u(a) + 0.5 * (double)C.kq[s] * (double)C.dt * (double)E[a];
             const double gm1 = sqrt(1.0 + um[0] * um[0] + um[1] * um[1] + um[2] * um[2]) - 1.0;
             acc[0] += (double)C.mass[s] * gm1;
             acc[1] += um[0]; acc[2] += um[1]; acc[3] += um[2];
