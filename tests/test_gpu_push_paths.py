@@ -36,3 +36,34 @@ def test_packed_moves(dims, fp64):
     assert np.abs(b1 - st.b).max() < tol * np.abs(st.b).max()
     assert s.diag(0)["flags"] == 0
     s.close()
+
+
+@pytest.mark.parametrize("fp64", [False, True])
+@pytest.mark.parametrize("kw", [{}, {"faraday4": True}, {"tile": (8, 4, 2)}], ids=["yee", "fourth_order", "tile842"])
+def test_particles_enter_empty_tiles(fp64, kw):
+    # all particles start in one corner tile of a box with an evolving field:
+    # the empty tiles still advance b, and take the particles that enter them
+    # without the overflow region (each tile has 32 slots to spare, and fewer
+    # than that enter any of them here)
+    rng = np.random.default_rng(77)
+    dims, n = (17, 12, 8), 40
+    s = G.sim(dims, 10.0, 40.0, [n, n], fp64=fp64, **kw)
+    st = G.oracle_state(dims, 10.0, 40.0)
+    st.faraday4 = bool(kw.get("faraday4"))
+    e, b = G.random_fields(rng, int(np.prod(dims)), 0.02, 0.2)
+    parts = [(rng.uniform(0, 3, (n, 3)), rng.standard_normal((n, 3))) for _ in range(2)]
+    G.start(s, st, parts, e=e, b=b, fp64=fp64)
+    tol = 1e-11 if fp64 else 2e-5
+    for _ in range(3):
+        s.step(4)
+        st.step(4)
+        e1, b1, _ = s.fields(0)
+        assert np.abs(e1 - st.e).max() < tol * np.abs(st.e).max()
+        assert np.abs(b1 - st.b).max() < tol * np.abs(st.b).max()
+        d = s.diag(0)
+        assert d["flags"] == 0 and d["count"].tolist() == [n, n] and d["n_overflow"].tolist() == [0, 0]
+    for sp in range(2):
+        x, u, _ = s.particles(0, sp)
+        assert np.abs(G.wrap_delta(x, st.x[st.species == sp], dims)).max() < 10 * tol
+        assert G.u_rel_err(u, st.u[st.species == sp], 1e-2).max() < 10 * tol
+    s.close()
