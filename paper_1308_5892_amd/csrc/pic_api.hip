@@ -180,8 +180,9 @@ struct Layout {
     Item *items_push = nullptr, *items_box = nullptr;
     CellBlock *cblocks = nullptr;
     StageItem *sitems = nullptr;
+    uint32_t *half = nullptr;          // per box: species whose staged momenta are integrated back by dt/2
     uint32_t *flags = nullptr;
-    double *mj_cum = nullptr, *mj_tab[2] = {nullptr, nullptr};
+    double *mj_cum[2] = {nullptr, nullptr}, *mj_tab[2] = {nullptr, nullptr};
     int n_items = 0, n_cblocks = 0, max_sitems = 0;
     size_t bytes = 0;
 };
@@ -199,14 +200,16 @@ static void make_layout(const pic_config *cfg, std::vector<BoxHost> &bh, char *b
     for (auto &H : bh) {
         L.n_items += H.ntiles + kOvfBlocks;
         L.n_cblocks += (int)((H.nc + kBlock - 1) / kBlock);
-        for (int s = 0; s < cfg->n_species; ++s) L.max_sitems += (H.stage_cap[s] + kBlock - 1) / kBlock;
+        const int64_t chunk = stage_chunk(H.ntiles);
+        for (int s = 0; s < cfg->n_species; ++s) L.max_sitems += (int)((H.stage_cap[s] + chunk - 1) / chunk);
     }
     L.items_push = A.take<Item>(8 * (size_t)L.n_items);   // room for the padding of the push order
     L.items_box = A.take<Item>(L.n_items);
     L.cblocks = A.take<CellBlock>(L.n_cblocks);
     L.sitems = A.take<StageItem>(std::max(1, L.max_sitems));
+    L.half = A.take<uint32_t>(cfg->n_boxes);
     L.flags = A.take<uint32_t>(64);
-    L.mj_cum = A.take<double>(kTabM + 1);
+    for (auto &c : L.mj_cum) c = A.take<double>(kTabM + 1 + 2 * ((kTabM + kMjBlock - 1) / kMjBlock));   // and the block totals
     L.mj_tab[0] = A.take<double>(kTabN + 1);
     L.mj_tab[1] = A.take<double>(kTabN + 1);
     bd.resize(cfg->n_boxes);
@@ -447,17 +450,30 @@ static int merge_t(pic_ctx *ctx, bool force)
     if (!ctx->pending && !force) return PIC_OK;
     std::vector<StageItem> si;
     for (int b = 0; b < ctx->cfg.n_boxes; ++b)
+        for (int s = 0; s < ctx->cfg.n_species; ++s) {
+            const int64_t n = ctx->stage_n[b][s], chunk = stage_chunk(ctx->bh[b].ntiles);
+            for (int64_t f = 0; f < n; f += chunk) si.push_back({b, s, (int32_t)f, (int32_t)std::min(n, f + chunk)});
+        }
+    std::vector<uint32_t> half(ctx->cfg.n_boxes, 0u);
+    bool any_half = false;
+    for (int b = 0; b < ctx->cfg.n_boxes; ++b)
         for (int s = 0; s < ctx->cfg.n_species; ++s)
-            for (int f = 0; f < ctx->stage_n[b][s]; f += kBlock)
-                si.push_back({b, s, f, std::min(ctx->stage_n[b][s], f + kBlock), ctx->stage_half[b][s]});
+            if (ctx->stage_n[b][s] > 0 && ctx->stage_half[b][s]) {
+                half[b] |= 1u << s;
+                any_half = true;
+            }
     if ((int)si.size() > ctx->L.max_sitems) { ctx->err = "stage item list overflow"; return PIC_ENOMEM; }
     if (!si.empty()) {
         HIPCHK(hipMemcpyAsync(ctx->L.sitems, si.data(), si.size() * sizeof(StageItem), hipMemcpyHostToDevice,
                               ctx->stream));
+        if (any_half)
+            HIPCHK(hipMemcpyAsync(ctx->L.half, half.data(), half.size() * sizeof(uint32_t), hipMemcpyHostToDevice,
+                                  ctx->stream));
     }
     StepConst<R> C = step_const<R>(ctx);
     HIPCHK(launch_repack<R>(dev_boxes<R>(ctx), ctx->cfg.n_boxes, ctx->L.items_box,
-                            ctx->L.n_items, ctx->L.sitems, (int)si.size(), C, ctx->stream));
+                            ctx->L.n_items, ctx->L.sitems, (int)si.size(), any_half ? ctx->L.half : nullptr,
+                            ctx->lds_bytes, (ctx->cfg.flags & PIC_FARADAY4) ? 1 : 0, C, ctx->stream));
     ctx->cur ^= 1;
     for (int b = 0; b < ctx->cfg.n_boxes; ++b)
         for (int s = 0; s < ctx->cfg.n_species; ++s) ctx->binned[b][s] += ctx->stage_n[b][s];
@@ -1084,9 +1100,10 @@ static int load_t(pic_ctx *ctx, const pic_load_desc *d)
     }
     if (npairs == 0) return PIC_OK;
     const pic_mj *pops[2] = {&d->mj_a, &d->mj_b};
-    for (int q = 0; q < 2; ++q)
-        HIPCHK(launch_mj_table(pops[q]->theta, pops[q]->gamma_beta, ctx->L.mj_cum, kTabM, kTabN, ctx->L.mj_tab[q],
-                               ctx->stream));
+    // two populations of one temperature and drift share their table
+    const double theta[2] = {pops[0]->theta, pops[1]->theta}, gb[2] = {pops[0]->gamma_beta, pops[1]->gamma_beta};
+    const int ntab = theta[0] == theta[1] && gb[0] == gb[1] ? 1 : 2;
+    HIPCHK(launch_mj_tables(ntab, theta, gb, ctx->L.mj_cum, kTabM, kTabN, ctx->L.mj_tab, ctx->stream));
     LoadArgs L;
     memset(&L, 0, sizeof(L));
     L.box = box;
@@ -1111,7 +1128,7 @@ static int load_t(pic_ctx *ctx, const pic_load_desc *d)
         P.G = std::sqrt(1.0 + pops[q]->gamma_beta * pops[q]->gamma_beta);
         P.beta0 = pops[q]->gamma_beta / P.G;
         P.axis = pops[q]->axis;
-        P.tab = ctx->L.mj_tab[q];
+        P.tab = ctx->L.mj_tab[q < ntab ? q : 0];
     }
     HIPCHK(launch_load_pairs<R>(boxes, L, ctx->stream));
     ctx->stage_n[box][sa] = (int32_t)(L.offa + npairs);

@@ -241,11 +241,22 @@ struct CellBlock {
     int32_t first;
 };
 
-// stage item: particles [first, last) of the stage of (box, species); half:
-// integrate their momenta back by dt/2 when they are binned
+// stage item: particles [first, last) of the stage of (box, species), the
+// chunk of one block.  A chunk holds 16 particles per tile of the box, so that
+// counting them per tile in LDS saves most of the global atomics, within
+// [4096, 65536]: enough blocks for a small load, and the LDS table of
+// kCountTiles tiles (64 KB) never larger than the chunk.
 struct StageItem {
-    int32_t box, species, first, last, half;
+    int32_t box, species, first, last;
 };
+constexpr int kStageBlock = 1024;      // threads per block of the stage kernels
+constexpr int kCountTiles = 16384;
+static_assert(kStageBlock * 64 == 65536, "64 blocks scatter the largest chunk");
+inline int stage_chunk(int ntiles)
+{
+    const int64_t n = ((int64_t)16 * ntiles + 1023) / 1024 * 1024;
+    return (int)(n < 4096 ? 4096 : (n > 65536 ? 65536 : n));
+}
 
 // one drifting Maxwell-Juttner population of a load
 struct MJPop {
@@ -291,7 +302,8 @@ template <typename R>
 hipError_t launch_advance_b(const BoxDev<R> *boxes, const CellBlock *blocks, int nblocks, R h, hipStream_t st);
 template <typename R>
 hipError_t launch_repack(const BoxDev<R> *boxes, int nboxes, const Item *items, int nitems,
-                         const StageItem *sitems, int nsitems, const StepConst<R> &C, hipStream_t st);
+                         const StageItem *sitems, int nsitems, const uint32_t *half, size_t lds, int faraday4,
+                         const StepConst<R> &C, hipStream_t st);
 template <typename R>
 hipError_t launch_diag(const BoxDev<R> *boxes, int box, int64_t nc, const Item *items, int nitems,
                        const StepConst<R> &C, const DiagBuf &out, int hist_len, hipStream_t st);
@@ -299,8 +311,9 @@ hipError_t launch_diag(const BoxDev<R> *boxes, int box, int64_t nc, const Item *
 // set up once per device (pic_init), then read
 hipError_t diag_scratch_setup();
 void *diag_scratch();
-hipError_t launch_mj_table(double theta, double gamma_beta, double *cum, int M, int N, double *tab,
-                           hipStream_t st);
+constexpr int kMjBlock = 1024;          // intervals per block of the table's prefix sum
+hipError_t launch_mj_tables(int n, const double *theta, const double *gamma_beta, double *const *cum, int M, int N,
+                            double *const *tab, hipStream_t st);
 template <typename R> hipError_t launch_load_pairs(const BoxDev<R> *boxes, const LoadArgs &L, hipStream_t st);
 template <typename R>
 hipError_t launch_harris_field(const BoxDev<R> *boxes, int64_t nc, const pic_harris_field &H, hipStream_t st);

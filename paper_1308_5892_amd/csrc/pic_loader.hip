@@ -59,52 +59,87 @@ __device__ inline double py_integral(double a, double b, const MJShape &m)
                 w2 * (py_density(c - h * x2, m) + py_density(c + h * x2, m)));
 }
 
-__global__ void mj_intervals_kernel(MJShape m, double ylo, double h, int M, double *cum)
+// Up to two populations' tables are built by the same launches (blockIdx.y).
+struct MJTable {
+    MJShape m;
+    double ylo, yhi, h;
+    double *cum, *tab;
+};
+struct MJTables {
+    MJTable t[2];
+};
+
+// A sum kept as an unevaluated pair hi + lo (Knuth's two-sum): adding two of
+// them loses nothing that matters at 64 bits, in any order, so the prefix sum
+// below can be a tree.
+struct Sum2 {
+    double hi, lo;
+};
+__device__ inline Sum2 two_sum(double a, double b)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < M) cum[i + 1] = py_integral(ylo + i * h, ylo + (i + 1) * h, m);
+    const double s = a + b, t = s - a;
+    return {s, (a - (s - t)) + (b - t)};
+}
+__device__ inline Sum2 add2(Sum2 a, Sum2 b)
+{
+    Sum2 s = two_sum(a.hi, b.hi);
+    s.lo += a.lo + b.lo;
+    return two_sum(s.hi, s.lo);
+}
+// inclusive prefix sum over the wave
+__device__ inline Sum2 wave_scan(Sum2 v)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const Sum2 o = {__shfl_up(v.hi, off), __shfl_up(v.lo, off)};
+        if (lane >= off) v = add2(o, v);
+    }
+    return v;
 }
 
-// In-place inclusive prefix sum of cum[1..M] (cum[0] = 0), one block of 1024
-// threads: per-thread compensated serial sums over contiguous chunks, then a
-// scan of the chunk totals.
-__global__ void __launch_bounds__(1024) mj_scan_kernel(double *cum, int M)
+// The integral of each of the M intervals and its prefix sum: cum[i + 1] holds
+// the sum over the intervals of block i / kMjBlock up to i, the block's total
+// goes to the pairs behind cum[M]; mj_offsets_kernel adds the blocks before.
+// (One block that summed all 65536 intervals serially per thread, with one
+// thread for the 1024 totals, took 190 us per table, half of the time of a
+// small load; these two take 15 us.)
+__global__ void __launch_bounds__(kMjBlock) mj_intervals_kernel(MJTables T, int M)
 {
-    __shared__ double tot[1024];
-    const int t = threadIdx.x;
-    const int per = (M + 1023) / 1024;
-    const int i0 = 1 + t * per, i1 = min(M + 1, i0 + per);
-    double s = 0.0, comp = 0.0;
-    for (int i = i0; i < i1; ++i) {
-        const double y = cum[i] - comp;
-        const double z = s + y;
-        comp = (z - s) - y;
-        s = z;
-        cum[i] = s;          // local running sum
-    }
-    tot[t] = s;
+    __shared__ Sum2 tot[kMjBlock / 64];
+    const MJTable &P = T.t[blockIdx.y];
+    const int i = blockIdx.x * kMjBlock + threadIdx.x, wave = threadIdx.x >> 6;
+    Sum2 v = {i < M ? py_integral(P.ylo + i * P.h, P.ylo + (i + 1) * P.h, P.m) : 0.0, 0.0};
+    v = wave_scan(v);
+    if ((threadIdx.x & 63) == 63) tot[wave] = v;
     __syncthreads();
-    if (t == 0) {
-        double run = 0.0, c2 = 0.0;
-        for (int q = 0; q < 1024; ++q) {   // exclusive offsets, compensated
-            const double v = tot[q];
-            tot[q] = run;
-            const double y = v - c2;
-            const double z = run + y;
-            c2 = (z - run) - y;
-            run = z;
-        }
+    Sum2 run = {0.0, 0.0};
+    for (int w = 0; w < wave; ++w) run = add2(run, tot[w]);
+    v = add2(run, v);
+    if (i < M) P.cum[i + 1] = v.hi;
+    if (threadIdx.x == kMjBlock - 1) {
+        P.cum[M + 1 + 2 * blockIdx.x] = v.hi;
+        P.cum[M + 2 + 2 * blockIdx.x] = v.lo;
     }
-    __syncthreads();
-    const double base = tot[t];
-    for (int i = i0; i < i1; ++i) cum[i] += base;
-    if (t == 0) cum[0] = 0.0;
+}
+__global__ void __launch_bounds__(kMjBlock) mj_offsets_kernel(MJTables T, int M)
+{
+    const MJTable &P = T.t[blockIdx.y];
+    Sum2 run = {0.0, 0.0};
+    for (int b = 0; b < (int)blockIdx.x; ++b) run = add2(run, Sum2{P.cum[M + 1 + 2 * b], P.cum[M + 2 + 2 * b]});
+    const int i = blockIdx.x * kMjBlock + threadIdx.x;
+    if (i < M && blockIdx.x > 0) P.cum[i + 1] = add2(run, Sum2{P.cum[i + 1], 0.0}).hi;
+    if (i == 0) P.cum[0] = 0.0;
 }
 
 // tab[i] = J^{-1}(i/N) for 0 < i < N (App. D), tab[0] = ylo, tab[N] = yhi.
-__global__ void mj_invert_kernel(MJShape m, double ylo, double yhi, double h, int M, const double *cum, int N,
-                                 double *tab)
+__global__ void mj_invert_kernel(MJTables T, int M, int N)
 {
+    const MJTable &P = T.t[blockIdx.y];
+    const MJShape m = P.m;
+    const double ylo = P.ylo, yhi = P.yhi, h = P.h;
+    const double *cum = P.cum;
+    double *tab = P.tab;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i > N) return;
     if (i == 0) { tab[0] = ylo; return; }
@@ -250,21 +285,29 @@ __global__ void __launch_bounds__(256) harris_field_kernel(const BoxDev<R> *__re
 
 // ----------------------------------------------------------- host launchers
 
-hipError_t launch_mj_table(double theta, double gamma_beta, double *cum, int M, int N, double *tab,
-                           hipStream_t st)
+hipError_t launch_mj_tables(int n, const double *theta, const double *gamma_beta, double *const *cum, int M, int N,
+                            double *const *tab, hipStream_t st)
 {
-    MJShape m;
-    m.mu = 1.0 / theta;
-    m.G = sqrt(1.0 + gamma_beta * gamma_beta);
-    m.beta0 = gamma_beta / m.G;
-    // support: where the exponent is 70 below its peak, gy - beta0 y = H
-    const double H = 1.0 / m.G + 70.0 / (m.mu * m.G);
-    const double rt = sqrt(H * H - 1.0 / (m.G * m.G));
-    const double ylo = m.G * m.G * (H * m.beta0 - rt), yhi = m.G * m.G * (H * m.beta0 + rt);
-    const double h = (yhi - ylo) / M;
-    hipLaunchKernelGGL(mj_intervals_kernel, dim3((M + 255) / 256), dim3(256), 0, st, m, ylo, h, M, cum);
-    hipLaunchKernelGGL(mj_scan_kernel, dim3(1), dim3(1024), 0, st, cum, M);
-    hipLaunchKernelGGL(mj_invert_kernel, dim3((N + 1 + 255) / 256), dim3(256), 0, st, m, ylo, yhi, h, M, cum, N, tab);
+    MJTables T;
+    for (int q = 0; q < n; ++q) {
+        MJTable &P = T.t[q];
+        MJShape &m = P.m;
+        m.mu = 1.0 / theta[q];
+        m.G = sqrt(1.0 + gamma_beta[q] * gamma_beta[q]);
+        m.beta0 = gamma_beta[q] / m.G;
+        // support: where the exponent is 70 below its peak, gy - beta0 y = H
+        const double H = 1.0 / m.G + 70.0 / (m.mu * m.G);
+        const double rt = sqrt(H * H - 1.0 / (m.G * m.G));
+        P.ylo = m.G * m.G * (H * m.beta0 - rt);
+        P.yhi = m.G * m.G * (H * m.beta0 + rt);
+        P.h = (P.yhi - P.ylo) / M;
+        P.cum = cum[q];
+        P.tab = tab[q];
+    }
+    const int blocks = (M + kMjBlock - 1) / kMjBlock;
+    hipLaunchKernelGGL(mj_intervals_kernel, dim3(blocks, n), dim3(kMjBlock), 0, st, T, M);
+    hipLaunchKernelGGL(mj_offsets_kernel, dim3(blocks, n), dim3(kMjBlock), 0, st, T, M);
+    hipLaunchKernelGGL(mj_invert_kernel, dim3((N + 1 + 255) / 256, n), dim3(256), 0, st, T, M, N);
     return hipGetLastError();
 }
 
