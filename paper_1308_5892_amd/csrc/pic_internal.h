@@ -251,7 +251,6 @@ struct StageItem {
 };
 constexpr int kStageBlock = 1024;      // threads per block of the stage kernels
 constexpr int kCountTiles = 16384;
-static_assert(kStageBlock * 64 == 65536, "64 blocks scatter the largest chunk");
 inline int stage_chunk(int ntiles)
 {
     const int64_t n = ((int64_t)16 * ntiles + 1023) / 1024 * 1024;
@@ -302,7 +301,7 @@ template <typename R>
 hipError_t launch_advance_b(const BoxDev<R> *boxes, const CellBlock *blocks, int nblocks, R h, hipStream_t st);
 template <typename R>
 hipError_t launch_repack(const BoxDev<R> *boxes, int nboxes, const Item *items, int nitems,
-                         const StageItem *sitems, int nsitems, const uint32_t *half, size_t lds, int faraday4,
+                         const StageItem *sitems, int nsitems, int split, const uint32_t *half, size_t lds, int faraday4,
                          const StepConst<R> &C, hipStream_t st);
 template <typename R>
 hipError_t launch_diag(const BoxDev<R> *boxes, int box, int64_t nc, const Item *items, int nitems,

@@ -2173,19 +2173,19 @@ __global__ void __launch_bounds__(kBlock) repack_scatter_kernel(const BoxDev<R> 
     }
 }
 
-// kStageSplit blocks per chunk, one particle per thread: the blocks that run
+// `split` blocks per chunk, one particle per thread: the blocks that run
 // together then write neighbouring places of the tiles (one block per chunk
-// took 5.7 ms for 33.5 M particles, this 3.0: 4-byte stores scattered over
+// took 5.7 ms for 33.5 M particles, this 2.9: 4-byte stores scattered over
 // every tile).
-constexpr int kStageSplit = 64;
 template <typename R>
 __global__ void __launch_bounds__(kStageBlock) repack_scatter_stage_kernel(const BoxDev<R> *__restrict__ boxes,
-                                                                           const StageItem *__restrict__ items, int dst)
+                                                                           const StageItem *__restrict__ items, int split,
+                                                                           int dst)
 {
-    const StageItem it = items[blockIdx.x / kStageSplit];
+    const StageItem it = items[blockIdx.x / split];
     const BoxDev<R> &B = boxes[it.box];
     const SpeciesDev<R> &S = B.sp[it.species];
-    const int p = it.first + (int)(blockIdx.x % kStageSplit) * kStageBlock + threadIdx.x;
+    const int p = it.first + (int)(blockIdx.x % split) * kStageBlock + threadIdx.x;
     if (p >= it.last) return;
     const int32_t cell = S.stage.cell[p];
     const int t = tile_of(B, cell), rank = S.buf[dst].cell[p];
@@ -2492,7 +2492,7 @@ hipError_t launch_advance_b(const BoxDev<R> *boxes, const CellBlock *blocks, int
 
 template <typename R>
 hipError_t launch_repack(const BoxDev<R> *boxes, int nboxes, const Item *items, int nitems,
-                         const StageItem *sitems, int nsitems, const uint32_t *half, size_t lds, int faraday4,
+                         const StageItem *sitems, int nsitems, int split, const uint32_t *half, size_t lds, int faraday4,
                          const StepConst<R> &C, hipStream_t st)
 {
     const int dst = C.cur ^ 1;
@@ -2502,8 +2502,8 @@ hipError_t launch_repack(const BoxDev<R> *boxes, int nboxes, const Item *items, 
     if (nitems) hipLaunchKernelGGL(repack_count_kernel<R>, dim3(nitems), dim3(kBlock), 0, st, boxes, items, C.nsp, C.cur);
     hipLaunchKernelGGL(repack_layout_kernel<R>, dim3(nboxes * C.nsp), dim3(kBlock), 0, st, boxes, C.nsp, dst, C.flags);
     if (nsitems)
-        hipLaunchKernelGGL(repack_scatter_stage_kernel<R>, dim3(nsitems * kStageSplit), dim3(kStageBlock), 0, st, boxes,
-                           sitems, dst);
+        hipLaunchKernelGGL(repack_scatter_stage_kernel<R>, dim3(nsitems * split), dim3(kStageBlock), 0, st, boxes, sitems,
+                           split, dst);
     if (half) {
         // before the binned particles follow the staged ones into the tiles
         auto go = [&](auto kern) -> hipError_t {
@@ -2702,7 +2702,7 @@ hipError_t launch_spectrum(const BoxDev<R> *boxes, int box, const int n[3], int 
                                          uint32_t *, hipStream_t);                                                        \
     template hipError_t launch_advance_b<R>(const BoxDev<R> *, const CellBlock *, int, R, hipStream_t);       \
     template hipError_t launch_repack<R>(const BoxDev<R> *, int, const Item *, int, const StageItem *, int,    \
-                                         const uint32_t *, size_t, int, const StepConst<R> &, hipStream_t);   \
+                                         int, const uint32_t *, size_t, int, const StepConst<R> &, hipStream_t); \
     template hipError_t launch_diag<R>(const BoxDev<R> *, int, int64_t, const Item *, int,                    \
                                        const StepConst<R> &, const DiagBuf &, int, hipStream_t);              \
     template hipError_t launch_spectrum<R>(const BoxDev<R> *, int, const int[3], int, int, int, R, double *,   \
