@@ -71,8 +71,8 @@ static size_t carve(Bump &A, const pic_config *cfg, std::vector<BoxHost> &bh, st
         D.b = A.take<R>(3 * H.nc);
         D.bn = A.take<R>(3 * H.nc);
         D.J = A.take<JT>(3 * H.nc);
+        D.acc = A.take<double>(kAccCopies * kAccLen) + (kAccCopies - 1) * kAccLen;
         D.rho = A.take<double>(H.nc);
-        D.acc = A.take<double>(kAccLen);
         D.hist = A.take<int64_t>((size_t)std::max(1, cfg->hist_bins) * kMaxSpecies);
         D.alpha0 = 2.0 / (H.cfg.n_x * H.cfg.n_x * H.cfg.rho0);
         D.wall = H.cfg.walls - 1;
@@ -661,18 +661,21 @@ static int check_box(pic_ctx *ctx, int box)
     return PIC_OK;
 }
 
+static int clear_flags(pic_ctx *ctx)
+{
+    uint32_t z = 0;
+    HIPCHK(hipMemcpyAsync(ctx->L.flags, &z, sizeof(z), hipMemcpyHostToDevice, ctx->stream));
+    HIPCHK(hipStreamSynchronize(ctx->stream));
+    return PIC_OK;
+}
+
 static int read_flags(pic_ctx *ctx, uint32_t *out)
 {
     uint32_t f = 0;
     HIPCHK(hipMemcpyAsync(&f, ctx->L.flags, sizeof(f), hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
-    if (f) {
-        uint32_t z = 0;
-        HIPCHK(hipMemcpyAsync(ctx->L.flags, &z, sizeof(z), hipMemcpyHostToDevice, ctx->stream));
-        HIPCHK(hipStreamSynchronize(ctx->stream));
-    }
     *out = f;
-    return PIC_OK;
+    return f ? clear_flags(ctx) : PIC_OK;
 }
 
 int pic_sync(pic_ctx *ctx)
@@ -757,15 +760,11 @@ static int diag_t(pic_ctx *ctx, int box, pic_diag_out *o, int64_t *hist, const D
     StepConst<R> C = step_const<R>(ctx);
     const int i0 = ctx->box_item_off[box], i1 = ctx->box_item_off[box + 1];
     HIPCHK(launch_diag<R>(boxes, box, D.nc, ctx->L.items_box + i0, i1 - i0, C, buf, hist_len, ctx->stream));
-    double acc[kAccLen];
+    double acc[kAccLen + kMaxSpecies + 1];   // sums, overflow counts, flags (diag_collect_kernel)
     HIPCHK(hipMemcpyAsync(acc, buf.acc, sizeof(acc), hipMemcpyDeviceToHost, ctx->stream));
     if (hist && ctx->cfg.hist_bins > 0)   // device layout [species][bins], as the caller's
         HIPCHK(hipMemcpyAsync(hist, buf.hist, (size_t)nsp * ctx->cfg.hist_bins * sizeof(int64_t),
                               hipMemcpyDeviceToHost, ctx->stream));
-    int32_t novf[kMaxSpecies] = {0, 0, 0, 0};
-    for (int s = 0; s < nsp; ++s)
-        HIPCHK(hipMemcpyAsync(&novf[s], D.sp[s].nb[ctx->cur] + D.ntiles, sizeof(int32_t), hipMemcpyDeviceToHost,
-                              ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
     memset(o, 0, sizeof(*o));
     o->t = ctx->step * ctx->cfg.dt;
@@ -782,13 +781,13 @@ static int diag_t(pic_ctx *ctx, int box, pic_diag_out *o, int64_t *hist, const D
         o->P[s][0] = a[1]; o->P[s][1] = a[2]; o->P[s][2] = a[3];
         o->n_particles[s] = (int64_t)std::llround(a[4]);
         o->sum_gm1[s] = a[5];
-        o->n_overflow[s] = std::min(novf[s], D.sp[s].ovf_cap);
+        o->n_overflow[s] = std::min((int32_t)acc[kAccLen + s], D.sp[s].ovf_cap);
     }
-    uint32_t f = 0;
-    int rc = read_flags(ctx, &f);
-    if (rc) return rc;
+    const uint32_t f = (uint32_t)acc[kAccLen + kMaxSpecies];
     o->flags = f;
     if (f) {
+        int rc = clear_flags(ctx);
+        if (rc) return rc;
         ctx->err = "device error flag raised: " + std::to_string(f);
         return PIC_EFLAG;
     }
@@ -804,10 +803,10 @@ int pic_diag(pic_ctx *ctx, int box, pic_diag_out *out, int64_t *hist)
     if (rc) return rc;
     if (ctx->fp64) {
         const BoxDev<double> &D = bdvec<double>(ctx)[box];
-        return diag_t<double>(ctx, box, out, hist, DiagBuf{D.acc, D.rho, D.hist});
+        return diag_t<double>(ctx, box, out, hist, DiagBuf{D.acc, D.rho, D.hist, kAccCopies});
     }
     const BoxDev<float> &D = bdvec<float>(ctx)[box];
-    return diag_t<float>(ctx, box, out, hist, DiagBuf{D.acc, D.rho, D.hist});
+    return diag_t<float>(ctx, box, out, hist, DiagBuf{D.acc, D.rho, D.hist, kAccCopies});
 }
 
 // Bytes of the static scratch that pic_diag_noalloc needs for box `box`:
@@ -843,7 +842,14 @@ int pic_diag_noalloc(pic_ctx *ctx, int box, pic_diag_out *out, int64_t *hist)
         return PIC_EDEVICE;
     }
     auto up = [](size_t v) { return (v + 255) & ~size_t(255); };
+    // as many copies of the accumulators as fit besides
+    const size_t more = (kAccCopies - 1) * kAccLen * sizeof(double);
     DiagBuf buf;
+    buf.copies = 1;
+    if (need + more <= kDiagScratchBytes) {
+        buf.copies = kAccCopies;
+        p += more;
+    }
     buf.acc = reinterpret_cast<double *>(p);
     buf.rho = reinterpret_cast<double *>(p + up(kAccLen * sizeof(double)));
     buf.hist = reinterpret_cast<int64_t *>(p + up(kAccLen * sizeof(double)) +

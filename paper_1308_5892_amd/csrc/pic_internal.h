@@ -158,7 +158,7 @@ struct BoxDev {
     PIC_GLOBAL R *bn;              // 3 * nc, the other b buffer: the push writes b^{t+dt/2} there
     PIC_GLOBAL typename JType<R>::T *J;   // 3 * nc, current of the step in flight
     PIC_GLOBAL double *rho;        // nc, diagnostic charge density
-    PIC_GLOBAL double *acc;        // diagnostic accumulators (kAccLen doubles)
+    PIC_GLOBAL double *acc;        // diagnostic accumulators (kAccLen doubles, the other copies before them)
     PIC_GLOBAL int64_t *hist;      // n_species * hist_bins
     double alpha0;                 // 2 / (n_x^2 rho0)
     int32_t wall;                  // axis with conducting walls, -1: periodic
@@ -185,6 +185,7 @@ struct StepConst {
 constexpr int kAccField = 0;       // [0..2] sum e^2/2, [3..5] sum (b^t)^2/2, [6] gauss max, [7] gauss sum sq
 constexpr int kAccSp = 8;          // then per species 6: K, P[3], count, sum(gamma-1)
 constexpr int kAccLen = kAccSp + 6 * kMaxSpecies;
+constexpr int kAccCopies = 16;     // blocks add to one of these many copies, so that fewer meet on an address
 
 // work item of the particle kernels: box, and tile (>= 0) or -1-k for overflow
 // block k; box -1 is an idle item (padding of the push order)
@@ -281,10 +282,16 @@ struct LoadArgs {
 // points it into the arena, pic_diag_noalloc into the library's static
 // scratch.
 struct DiagBuf {
-    PIC_GLOBAL double *acc;
-    PIC_GLOBAL double *rho;
-    PIC_GLOBAL int64_t *hist;
+    PIC_GLOBAL double *acc;        // copy 0; copy r lies r * kAccLen before it
+    PIC_GLOBAL double *rho;        // right behind acc
+    PIC_GLOBAL int64_t *hist;      // behind rho
+    int copies;
+    __host__ __device__ PIC_GLOBAL double *copy(unsigned block) const
+    {
+        return acc - (int64_t)(block % (unsigned)copies) * kAccLen;
+    }
 };
+static_assert(kAccLen * sizeof(double) % 256 == 0, "rho follows acc in 256-byte aligned buffers");
 
 // size of the static scratch of pic_diag_noalloc (per GPU)
 constexpr size_t kDiagScratchBytes = size_t(32) << 20;

@@ -8,6 +8,7 @@
 // the production form (int64 fixed-point current), double the FP64 form.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <limits>
 
 #include "pic_internal.h"
@@ -2266,138 +2267,165 @@ __global__ void __launch_bounds__(kBlock) clear_counts_kernel(const BoxDev<R> *_
 
 // -------------------------------------------------------------- diagnostics
 
-template <typename R>
-__device__ inline void block_sum_to(double *dst, double v)
+__device__ inline double wave_sum(double v)
 {
-    __shared__ double red[kBlock / 64];
     for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off);
-    const int w = threadIdx.x >> 6;
-    __syncthreads();
-    if (__lane_id() == 0) red[w] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int q = 0; q < kBlock / 64; ++q) t += red[q];
-        atomicAdd(dst, t);
+    return v;
+}
+
+// Histogram bin of a particle with gamma - 1 = g: that of the FP64 logarithm.
+// An FP32 logarithm decides it unless it falls within its error of an edge
+// (relative error 2^-21 of the logarithm and of its operands, taken four
+// times; every lane near an edge, beyond FP32's range, or with bins finer than
+// that takes the FP64 one): a quarter of the kernel's FP64 work.
+__device__ inline int gamma_bin(double g, double lo, double hi, int bins)
+{
+    const float l = 0.30102999566398120f * __builtin_amdgcn_logf((float)g), scale = (float)(bins / (hi - lo));
+    const float x = (l - (float)lo) * scale, f = floorf(x);
+    const float err = 2e-6f * (scale * (fabsf(l) + fabsf((float)lo) + 1.0f) + fabsf(x));
+    int bin = (int)f;
+    if (!(g > 1e-30 && g < 1e30 && x - f > err && f + 1.0f - x > err)) {
+        const double v = log10(g > 1e-300 ? g : 1e-300);
+        bin = (int)floor((v - lo) / (hi - lo) * bins);
     }
+    return bin < 0 ? 0 : (bin >= bins ? bins - 1 : bin);
 }
 
 // Per-particle diagnostics of one box (items of that box only): gamma^t from
 // u^- = u^{t-dt/2} + (k dt/2) E(x^t) (READING: the mover's own gamma^t), the
-// k = 0 momentum, the gamma-1 histogram and the CIC charge density.  A tile
-// item stages the node-averaged e of its (t+1)^3 nodes in LDS once and sums its
-// charge and histogram there (one global atomic per node and bin); the
-// overflow items gather from HBM and add to the global sums directly.
+// k = 0 momentum, the gamma-1 histogram and the CIC charge density.  A block
+// takes every gridDim.x-th item.  A tile item stages the node-averaged e of its
+// (t+1)^3 nodes in LDS once and sums its charge there (one global atomic per
+// node); the overflow items gather from HBM and add to the global charge
+// directly.  The six sums per species and the histogram stay in LDS until the
+// block ends: their global atomics all meet on a few addresses, where each
+// takes about 8 ns.  One set per tile and species took 3.19 ms on a box of 31442
+// tiles (15.7 M particles), this 0.35; 0.64 and 0.46 ms on one of 4096 (33.5 M),
+// where the FP64 arithmetic and the LDS atomics of the charge bound it now.
 constexpr int kDiagNodes = 9 * 9 * 9;   // nodes of the largest tile (8^3 cells)
 constexpr int kDiagHist = 512;          // histograms up to this many bins are summed in LDS
+constexpr int kDiagBlocks = 2048;       // at most, eight per CU
 template <typename R>
 __global__ void __launch_bounds__(kBlock) diag_particles_kernel(const BoxDev<R> *__restrict__ boxes,
-                                                                const Item *__restrict__ items, StepConst<R> C,
-                                                                DiagBuf out)
+                                                                const Item *__restrict__ items, int nitems,
+                                                                StepConst<R> C, DiagBuf out)
 {
+    extern __shared__ unsigned shist[];             // [species][bins]
     __shared__ R sE[3 * kDiagNodes];
     __shared__ double srho[kDiagNodes];
-    __shared__ unsigned shist[kDiagHist];
-    const Item it = items[blockIdx.x];
-    const BoxDev<R> &B = boxes[it.box];
+    __shared__ double sacc[kBlock / 64][6 * kMaxSpecies];
     const R hdt = R(0.5) * C.dt;
-    const int tid = threadIdx.x;
-    const bool in_tile = it.tile >= 0;
-    TileGeom<R> g{};
-    if (in_tile) {
-        g = tile_geom<R>(B, it.tile);
-        // node-averaged e (App. A.3.3)
-        for (int q = tid; q < g.NN; q += kBlock) {
-            const int i = g.o[0] + q % g.NX, j = g.o[1] + (q / g.NX) % g.NY, k = g.o[2] + q / (g.NX * g.NY);
-            sE[q] = node_value_global(B, 0, i, j, k, R(0));
-            sE[g.NN + q] = node_value_global(B, 1, i, j, k, R(0));
-            sE[2 * g.NN + q] = node_value_global(B, 2, i, j, k, R(0));
-            srho[q] = 0.0;
-        }
-    }
+    const int tid = threadIdx.x, wave = tid >> 6;
     const bool lhist = C.hist_bins > 0 && C.hist_bins <= kDiagHist;
-    for (int s = 0; s < C.nsp; ++s) {
-        const SpeciesDev<R> &S = B.sp[s];
-        int first, stride;
-        const TileRanges r = item_range(B, S, C.cur, it.tile, first, stride);
-        const PBuf<R> &P = S.buf[C.cur];
-        if (lhist)
-            for (int q = tid; q < C.hist_bins; q += kBlock) shist[q] = 0u;
-        __syncthreads();
-        const double q = (double)C.qs[s] * B.alpha0;
-        double acc[6] = {0, 0, 0, 0, 0, 0};
-        for (int p = first; p < r.n; p += stride) {
-            const int idx = r.slot(p);
-            const PSlot<R> ps = slot_at(P, idx);
-            const int32_t cell = in_tile ? local_cell(B, g.o, ps.code()) : P.cell[idx];
-            const int ix = cell_x(cell), iy = cell_y(cell), iz = cell_z(cell);
-            R d[3] = {ps.d(0), ps.d(1), ps.d(2)};
-            R E[3];
-            int nb = 0;
-            if (in_tile) {
-                // the cell's trilinear interpolant, as the push evaluates it
-                nb = (ix - g.o[0]) + g.NX * ((iy - g.o[1]) + g.NY * (iz - g.o[2]));
-
-                for (int c = 0; c < 3; ++c) {
-                    const R *F = sE + c * g.NN + nb;
-                    const int NX = g.NX, NXY = g.NX * g.NY;
-                    const R f[8] = {F[0], F[1], F[NX], F[1 + NX], F[NXY], F[1 + NXY], F[NX + NXY], F[1 + NX + NXY]};
-                    R cf[8];
-                    trilinear_coef(f, cf);
-                    E[c] = trilinear_eval(cf, d);
-                }
-            } else {
-                R Bf[3];
-                gather_global(B, ix, iy, iz, d, hdt, E, Bf);
+    if (lhist)
+        for (int q = tid; q < C.nsp * C.hist_bins; q += kBlock) shist[q] = 0u;
+    if (tid < kBlock / 64 * 6 * kMaxSpecies) (&sacc[0][0])[tid] = 0.0;
+    __syncthreads();
+    for (int item = blockIdx.x; item < nitems; item += gridDim.x) {
+        const Item it = items[item];
+        const BoxDev<R> &B = boxes[it.box];
+        const bool in_tile = it.tile >= 0;
+        TileGeom<R> g{};
+        if (in_tile) {
+            int n = 0;
+            for (int s = 0; s < C.nsp; ++s) n += tile_ranges(B.sp[s], C.cur, it.tile).n;
+            if (n == 0) continue;
+            g = tile_geom<R>(B, it.tile);
+            // node-averaged e (App. A.3.3)
+            for (int q = tid; q < g.NN; q += kBlock) {
+                const int i = g.o[0] + q % g.NX, j = g.o[1] + (q / g.NX) % g.NY, k = g.o[2] + q / (g.NX * g.NY);
+                sE[q] = node_value_global(B, 0, i, j, k, R(0));
+                sE[g.NN + q] = node_value_global(B, 1, i, j, k, R(0));
+                sE[2 * g.NN + q] = node_value_global(B, 2, i, j, k, R(0));
+                srho[q] = 0.0;
             }
-            double um[3];
-            for (int a = 0; a < 3; ++a)
-                um[a] = (double)ps.u(a) + 0.5 * (double)C.kq[s] * (double)C.dt * (double)E[a];
-            const double gm1 = sqrt(1.0 + um[0] * um[0] + um[1] * um[1] + um[2] * um[2]) - 1.0;
-            acc[0] += (double)C.mass[s] * gm1;
-            acc[1] += um[0]; acc[2] += um[1]; acc[3] += um[2];
-            acc[4] += 1.0;
-            acc[5] += gm1;
-            if (C.hist_bins > 0) {
-                const double v = log10(gm1 > 1e-300 ? gm1 : 1e-300);
-                int bin = (int)floor((v - C.hist_lo) / (C.hist_hi - C.hist_lo) * C.hist_bins);
-                bin = bin < 0 ? 0 : (bin >= C.hist_bins ? C.hist_bins - 1 : bin);
-                if (lhist) atomicAdd(&shist[bin], 1u);
-                else atomicAdd(reinterpret_cast<unsigned long long *>(&out.hist[s * C.hist_bins + bin]), 1ull);
-            }
-            for (int kk = 0; kk < 2; ++kk)
-                for (int jj = 0; jj < 2; ++jj)
-                    for (int ii = 0; ii < 2; ++ii) {
-                        const double w = (ii ? (double)d[0] : 1.0 - (double)d[0]) *
-                                         (jj ? (double)d[1] : 1.0 - (double)d[1]) *
-                                         (kk ? (double)d[2] : 1.0 - (double)d[2]);
-                        if (in_tile) {
-                            atomicAdd(&srho[nb + ii + g.NX * (jj + g.NY * kk)], q * w);
-                        } else {
-                            const int i = wrap_idx(ix + ii, B.n[0]), j = wrap_idx(iy + jj, B.n[1]),
-                                      k = wrap_idx(iz + kk, B.n[2]);
-                            atomicAdd(&out.rho[i + (int64_t)B.n[0] * (j + (int64_t)B.n[1] * k)], q * w);
-                        }
+            __syncthreads();
+        }
+        for (int s = 0; s < C.nsp; ++s) {
+            const SpeciesDev<R> &S = B.sp[s];
+            int first, stride;
+            const TileRanges r = item_range(B, S, C.cur, it.tile, first, stride);
+            const PBuf<R> P = S.buf[C.cur];
+            const double q = (double)C.qs[s] * B.alpha0, hk = 0.5 * (double)C.kq[s] * (double)C.dt;
+            double acc[6] = {0, 0, 0, 0, 0, 0};
+            for (int p = first; p < r.n; p += stride) {
+                const int idx = r.slot(p);
+                const PSlot<R> ps = slot_at(P, idx);
+                const int32_t cell = in_tile ? local_cell(B, g.o, ps.code()) : P.cell[idx];
+                const int ix = cell_x(cell), iy = cell_y(cell), iz = cell_z(cell);
+                const R d[3] = {ps.d(0), ps.d(1), ps.d(2)}, u[3] = {ps.u(0), ps.u(1), ps.u(2)};
+                R E[3];
+                int nb = 0;
+                if (in_tile) {
+                    // the cell's trilinear interpolant, as the push evaluates it
+                    nb = (ix - g.o[0]) + g.NX * ((iy - g.o[1]) + g.NY * (iz - g.o[2]));
+                    for (int c = 0; c < 3; ++c) {
+                        const R *F = sE + c * g.NN + nb;
+                        const int NX = g.NX, NXY = g.NX * g.NY;
+                        const R f[8] = {F[0],   F[1],       F[NX],       F[1 + NX],
+                                        F[NXY], F[1 + NXY], F[NX + NXY], F[1 + NX + NXY]};
+                        R cf[8];
+                        trilinear_coef(f, cf);
+                        E[c] = trilinear_eval(cf, d);
                     }
-        }
-        for (int k = 0; k < 6; ++k) block_sum_to<R>(&out.acc[kAccSp + 6 * s + k], acc[k]);
-        if (lhist) {
-            __syncthreads();
-            for (int b = tid; b < C.hist_bins; b += kBlock)
-                if (shist[b]) atomicAdd(reinterpret_cast<unsigned long long *>(&out.hist[s * C.hist_bins + b]),
-                                        (unsigned long long)shist[b]);
-            __syncthreads();
-        }
-    }
-    if (in_tile) {
-        __syncthreads();
-        for (int q = tid; q < g.NN; q += kBlock)
-            if (srho[q] != 0.0) {
-                const int i = wrap_idx(g.o[0] + q % g.NX, B.n[0]), j = wrap_idx(g.o[1] + (q / g.NX) % g.NY, B.n[1]),
-                          k = wrap_idx(g.o[2] + q / (g.NX * g.NY), B.n[2]);
-                atomicAdd(&out.rho[i + (int64_t)B.n[0] * (j + (int64_t)B.n[1] * k)], srho[q]);
+                } else {
+                    R Bf[3];
+                    gather_global(B, ix, iy, iz, d, hdt, E, Bf);
+                }
+                double um[3];
+                for (int a = 0; a < 3; ++a) um[a] = (double)u[a] + hk * (double)E[a];
+                const double gm1 = sqrt(1.0 + um[0] * um[0] + um[1] * um[1] + um[2] * um[2]) - 1.0;
+                acc[0] += (double)C.mass[s] * gm1;
+                acc[1] += um[0]; acc[2] += um[1]; acc[3] += um[2];
+                acc[4] += 1.0;
+                acc[5] += gm1;
+                if (C.hist_bins > 0) {
+                    const int bin = s * C.hist_bins + gamma_bin(gm1, C.hist_lo, C.hist_hi, C.hist_bins);
+                    if (lhist) atomicAdd(&shist[bin], 1u);
+                    else atomicAdd(reinterpret_cast<unsigned long long *>(&out.hist[bin]), 1ull);
+                }
+                for (int kk = 0; kk < 2; ++kk)
+                    for (int jj = 0; jj < 2; ++jj)
+                        for (int ii = 0; ii < 2; ++ii) {
+                            const double w = (ii ? (double)d[0] : 1.0 - (double)d[0]) *
+                                             (jj ? (double)d[1] : 1.0 - (double)d[1]) *
+                                             (kk ? (double)d[2] : 1.0 - (double)d[2]);
+                            if (in_tile) {
+                                atomicAdd(&srho[nb + ii + g.NX * (jj + g.NY * kk)], q * w);
+                            } else {
+                                const int i = wrap_idx(ix + ii, B.n[0]), j = wrap_idx(iy + jj, B.n[1]),
+                                          k = wrap_idx(iz + kk, B.n[2]);
+                                atomicAdd(&out.rho[i + (int64_t)B.n[0] * (j + (int64_t)B.n[1] * k)], q * w);
+                            }
+                        }
             }
+            if (r.n > 0)
+                for (int k = 0; k < 6; ++k) {
+                    const double v = wave_sum(acc[k]);
+                    if (__lane_id() == 0) sacc[wave][6 * s + k] += v;
+                }
+        }
+        if (in_tile) {
+            __syncthreads();
+            for (int q = tid; q < g.NN; q += kBlock)
+                if (srho[q] != 0.0) {
+                    const int i = wrap_idx(g.o[0] + q % g.NX, B.n[0]), j = wrap_idx(g.o[1] + (q / g.NX) % g.NY, B.n[1]),
+                              k = wrap_idx(g.o[2] + q / (g.NX * g.NY), B.n[2]);
+                    atomicAdd(&out.rho[i + (int64_t)B.n[0] * (j + (int64_t)B.n[1] * k)], srho[q]);
+                }
+            __syncthreads();                            // before the next tile's nodes
+        }
     }
+    __syncthreads();
+    if (tid < 6 * C.nsp) {
+        double t = 0.0;
+        for (int w = 0; w < kBlock / 64; ++w) t += sacc[w][tid];
+        if (t != 0.0) atomicAdd(out.copy(blockIdx.x) + kAccSp + tid, t);
+    }
+    if (lhist)
+        for (int q = tid; q < C.nsp * C.hist_bins; q += kBlock)
+            if (shist[q])
+                atomicAdd(reinterpret_cast<unsigned long long *>(&out.hist[q]), (unsigned long long)shist[q]);
 }
 
 __device__ inline void atomic_max_pos(double *p, double v)
@@ -2406,23 +2434,25 @@ __device__ inline void atomic_max_pos(double *p, double v)
 }
 
 // Field energies (e^t, b^t) and the Gauss-law residual div e - rho at the nodes.
+// A few blocks stride over the cells, so that the sums' atomics stay few (one
+// block per 256 cells: 0.14 ms on 64^3 cells and 1.03 ms on 796 x 632 x 4).
+constexpr int kDiagFieldBlocks = 1024;
 template <typename R>
 __global__ void __launch_bounds__(kBlock) diag_fields_kernel(const BoxDev<R> *__restrict__ boxes, int box,
                                                              R dt, int filter, DiagBuf out)
 {
+    __shared__ double red[kBlock / 64][8];
     const BoxDev<R> &B = boxes[box];
-    const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    double v[7] = {0, 0, 0, 0, 0, 0, 0};
-    double gmax = 0.0;
-    if (p < B.nc) {
+    double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};             // [6]: the largest residual, [7]: the sum of squares
+    for (int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x; p < B.nc; p += (int64_t)gridDim.x * kBlock) {
         const int n0 = B.n[0], n1 = B.n[1];
         int i, j, k;
         cell_coords(p, n0, n1, i, j, k);
         for (int c = 0; c < 3; ++c) {
             const double ec = (double)B.e[c * B.nc + p];
             const double bc = (double)bt_global(B, c, i, j, k, R(0.5) * dt);
-            v[c] = 0.5 * ec * ec;
-            v[3 + c] = 0.5 * bc * bc;
+            v[c] += 0.5 * ec * ec;
+            v[3 + c] += 0.5 * bc * bc;
         }
         const double div = (double)fld(B.e, B, 0, i, j, k) - (double)fld(B.e, B, 0, i - 1, j, k) +
                            (double)fld(B.e, B, 1, i, j, k) - (double)fld(B.e, B, 1, i, j - 1, k) +
@@ -2431,13 +2461,46 @@ __global__ void __launch_bounds__(kBlock) diag_fields_kernel(const BoxDev<R> *__
         const double rho = filter ? smooth27<double>(out.rho, B.n, i, j, k) / 64.0 : out.rho[p];
         const bool on_wall = B.wall >= 0 && (B.wall == 0 ? i : (B.wall == 1 ? j : k)) == 0;
         const double r = on_wall ? 0.0 : div - rho;   // a wall plane carries the conductor's surface charge
-        v[6] = r * r;
-        gmax = fabs(r);
+        v[7] += r * r;
+        v[6] = fmax(v[6], fabs(r));
     }
-    for (int q = 0; q < 6; ++q) block_sum_to<R>(&out.acc[kAccField + q], v[q]);
-    block_sum_to<R>(&out.acc[kAccField + 7], v[6]);
-    for (int off = 32; off > 0; off >>= 1) gmax = fmax(gmax, __shfl_down(gmax, off));
-    if (__lane_id() == 0) atomic_max_pos(&out.acc[kAccField + 6], gmax);
+    const int wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        double t = v[q];
+        for (int off = 32; off > 0; off >>= 1) {
+            const double o = __shfl_down(t, off);
+            t = q == 6 ? fmax(t, o) : t + o;
+        }
+        if (__lane_id() == 0) red[wave][q] = t;
+    }
+    __syncthreads();
+    if (threadIdx.x < 8) {
+        const int q = threadIdx.x;
+        double t = red[0][q];
+        for (int w = 1; w < kBlock / 64; ++w) t = q == 6 ? fmax(t, red[w][q]) : t + red[w][q];
+        double *dst = (double *)(out.copy(blockIdx.x) + kAccField + q);
+        if (q == 6) atomic_max_pos(dst, t);
+        else atomicAdd(dst, t);
+    }
+}
+
+// The last diagnostics kernel: the copies of the accumulators added up, and
+// the overflow counts and the error flag word put behind them (over the charge
+// density, which is no longer needed), so that one copy brings all to the host.
+template <typename R>
+__global__ void __launch_bounds__(64) diag_collect_kernel(const BoxDev<R> *__restrict__ boxes, int box, StepConst<R> C,
+                                                          DiagBuf out)
+{
+    const BoxDev<R> &B = boxes[box];
+    const int q = threadIdx.x;
+    if (q < kAccLen) {
+        double t = out.acc[q];
+        for (int r = 1; r < out.copies; ++r) t = q == kAccField + 6 ? fmax(t, out.copy(r)[q]) : t + out.copy(r)[q];
+        out.acc[q] = t;
+    }
+    if (q < kMaxSpecies) out.rho[q] = q < C.nsp ? (double)B.sp[q].nb[C.cur][B.ntiles] : 0.0;
+    if (q == kMaxSpecies) out.rho[q] = (double)*C.flags;
 }
 
 // ----------------------------------------------------------- host launchers
@@ -2539,14 +2602,18 @@ hipError_t launch_diag(const BoxDev<R> *boxes, int box, int64_t nc, const Item *
                        const StepConst<R> &C, const DiagBuf &out, int hist_len, hipStream_t st)
 {
     // the accumulators, the charge density and the histogram start from zero
-    const int zb = 1024;
-    hipLaunchKernelGGL(zero_words_kernel, dim3(zb), dim3(kBlock), 0, st, (uint64_t *)out.acc, (int64_t)kAccLen);
-    hipLaunchKernelGGL(zero_words_kernel, dim3(zb), dim3(kBlock), 0, st, (uint64_t *)out.rho, nc);
-    hipLaunchKernelGGL(zero_words_kernel, dim3(zb), dim3(kBlock), 0, st, (uint64_t *)out.hist, (int64_t)hist_len);
+    // (they follow each other in memory)
+    PIC_GLOBAL double *first = out.copy(out.copies - 1);
+    const int64_t words = (PIC_GLOBAL double *)out.hist + hist_len - first;
+    hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)std::min<int64_t>(1024, (words + kBlock - 1) / kBlock)),
+                       dim3(kBlock), 0, st, (uint64_t *)first, words);
+    const size_t lhist = C.hist_bins <= kDiagHist ? (size_t)C.nsp * C.hist_bins * sizeof(unsigned) : 0;
     if (nitems)
-        hipLaunchKernelGGL(diag_particles_kernel<R>, dim3(nitems), dim3(kBlock), 0, st, boxes, items, C, out);
-    const int nb = (int)((nc + kBlock - 1) / kBlock);
+        hipLaunchKernelGGL(diag_particles_kernel<R>, dim3(std::min(nitems, kDiagBlocks)), dim3(kBlock), lhist, st, boxes,
+                           items, nitems, C, out);
+    const int nb = (int)std::min<int64_t>(kDiagFieldBlocks, (nc + kBlock - 1) / kBlock);
     hipLaunchKernelGGL(diag_fields_kernel<R>, dim3(nb), dim3(kBlock), 0, st, boxes, box, C.dt, C.filter, out);
+    hipLaunchKernelGGL(diag_collect_kernel<R>, dim3(1), dim3(64), 0, st, boxes, box, C, out);
     return hipGetLastError();
 }
 
