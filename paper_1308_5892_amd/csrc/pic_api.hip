@@ -239,6 +239,10 @@ using namespace pic;
 constexpr int kWatch = 4, kWatchLag = 2;
 constexpr uint32_t kWatchLimit = 500;
 
+// pinned host memory of a context: the watch's slots, then a buffer for small
+// copies
+constexpr size_t kPinnedBytes = 512 * 1024;
+
 struct pic_ctx {
     pic_config cfg;
     std::vector<pic_box> boxes;
@@ -271,6 +275,7 @@ struct pic_ctx {
     std::vector<hipEvent_t> ev_pool;
     uint32_t *watch_host = nullptr;          // pinned, coherent, kWatch slots
     uint32_t *watch_dev = nullptr;           // the same slots as the device addresses them
+    char *pinned = nullptr;                  // kPinnedBytes behind the slots
     hipEvent_t watch_ev[kWatch] = {};
     int64_t watch_step[kWatch] = {-1, -1, -1, -1};
     int64_t last_repack = 0;
@@ -612,13 +617,14 @@ int pic_init(const pic_config *cfg, void *dev_arena, size_t bytes, void *hip_str
     ctx->next_id.assign(cfg->n_boxes, std::vector<int32_t>(kMaxSpecies, 0));
     // the e update writes the watch straight into these slots (coherent, so
     // the host reads it once the step's event has completed): no copy per step
-    if (hipHostMalloc(reinterpret_cast<void **>(&ctx->watch_host), kWatch * sizeof(uint32_t),
-                      hipHostMallocCoherent) != hipSuccess) {
+    if (hipHostMalloc(reinterpret_cast<void **>(&ctx->watch_host), 256 + kPinnedBytes, hipHostMallocCoherent) !=
+        hipSuccess) {
         ctx->watch_host = nullptr;
         delete ctx;
         return PIC_EDEVICE;
     }
     for (int i = 0; i < kWatch; ++i) ctx->watch_host[i] = 0;
+    ctx->pinned = reinterpret_cast<char *>(ctx->watch_host) + 256;
     if (hipHostGetDevicePointer(reinterpret_cast<void **>(&ctx->watch_dev), ctx->watch_host, 0) != hipSuccess) {
         delete ctx;
         return PIC_EDEVICE;
@@ -884,8 +890,9 @@ int pic_field_spectrum(pic_ctx *ctx, int box, int field, int comp, int normal_ax
                      : spectrum_t<float>(ctx, box, field, comp, normal_axis, ps);
 }
 
+// Read-back with ids that are not 0 .. n - 1: ordered on the host.
 template <typename R>
-static int get_particles_t(pic_ctx *ctx, int box, int s, double *x, double *u, int32_t *id, int64_t *n)
+static int get_particles_sorted(pic_ctx *ctx, int box, int s, double *x, double *u, int32_t *id, int64_t *n)
 {
     const BoxDev<R> &D = bdvec<R>(ctx)[box];
     const SpeciesDev<R> &S = D.sp[s];
@@ -947,6 +954,59 @@ static int get_particles_t(pic_ctx *ctx, int box, int s, double *x, double *u, i
     return PIC_OK;
 }
 
+// Particles to the host.  They are ordered and converted on the GPU into the
+// slots of the copy that the next push overwrites, in as many passes as the
+// output has chunks of that size (two in the FP32 form), and copied from there
+// into the caller's arrays.  (Ordered and converted by the host, half a million
+// particles with ids took 42 ms; this takes 3.3, most of it fresh pages.)
+template <typename R>
+static int get_particles_t(pic_ctx *ctx, int box, int s, double *x, double *u, int32_t *id, int64_t *n)
+{
+    const BoxDev<R> &D = bdvec<R>(ctx)[box];
+    const SpeciesDev<R> &S = D.sp[s];
+    const BoxDev<R> *boxes = dev_boxes<R>(ctx);
+    const Item *items = ctx->L.items_box + ctx->box_item_off[box];
+    const int nitems = ctx->box_item_off[box + 1] - ctx->box_item_off[box];
+    const PBuf<R> &P = S.buf[ctx->cur];
+    char *scratch = reinterpret_cast<char *>(S.buf[ctx->cur ^ 1].rec);
+    const size_t bytes = PBuf<R>::bytes(S.slots);
+    int32_t *dinfo = reinterpret_cast<int32_t *>(ctx->L.flags) + 16, info[2] = {0, 0};   // behind the flag word
+    HIPCHK(launch_particle_offsets<R>(boxes, box, s, ctx->cur, dinfo, ctx->stream));
+    HIPCHK(hipMemcpyAsync(info, dinfo, sizeof(info), hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(hipStreamSynchronize(ctx->stream));
+    const int total = info[0];
+    int rc = PIC_OK;
+    if (*n < total) {
+        ctx->err = "output arrays too small";
+        rc = PIC_ENOMEM;
+    } else if (P.id && total > 0) {
+        HIPCHK(launch_zero(scratch, (total + 63) / 64, ctx->stream));
+        HIPCHK(launch_particle_ids<R>(boxes, items, nitems, s, ctx->cur, total, reinterpret_cast<uint32_t *>(scratch), dinfo,
+                                      ctx->stream));
+        HIPCHK(hipMemcpyAsync(info, dinfo, sizeof(info), hipMemcpyDeviceToHost, ctx->stream));
+        HIPCHK(hipStreamSynchronize(ctx->stream));
+    }
+    if (rc == PIC_OK && !info[1]) {
+        const int chunk = (int)std::max<size_t>(1, bytes / (6 * sizeof(double) + sizeof(int32_t)) - 1);
+        double *dx = reinterpret_cast<double *>(scratch), *du = dx + 3 * (size_t)chunk;
+        int32_t *di = reinterpret_cast<int32_t *>(du + 3 * (size_t)chunk);
+        for (int lo = 0; lo < total; lo += chunk) {
+            const int hi = (int)std::min<int64_t>(total, (int64_t)lo + chunk);
+            const size_t m = hi - lo;
+            HIPCHK(launch_particles_out<R>(boxes, items, nitems, s, ctx->cur, P.id ? 1 : 0, lo, hi, dx, du, di, ctx->stream));
+            if (x) HIPCHK(hipMemcpyAsync(x + 3 * (size_t)lo, dx, 3 * m * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+            if (u) HIPCHK(hipMemcpyAsync(u + 3 * (size_t)lo, du, 3 * m * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+            if (id) HIPCHK(hipMemcpyAsync(id + lo, di, m * sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream));
+        }
+    }
+    // the repack expects its counts cleared
+    HIPCHK(hipMemsetAsync(S.tcount, 0, (D.ntiles + 1) * sizeof(int32_t), ctx->stream));
+    HIPCHK(hipStreamSynchronize(ctx->stream));
+    if (rc == PIC_OK && info[1]) return get_particles_sorted<R>(ctx, box, s, x, u, id, n);
+    *n = total;
+    return rc;
+}
+
 int pic_get_particles(pic_ctx *ctx, int box, int species, double *x, double *u, int32_t *id, int64_t *n)
 {
     int rc = check_box(ctx, box);
@@ -969,36 +1029,19 @@ static int set_particles_t(pic_ctx *ctx, int box, int s, const double *x, const 
     HIPCHK(hipMemsetAsync(S.na[ctx->cur], 0, (D.ntiles + 1) * sizeof(int32_t), ctx->stream));
     HIPCHK(hipMemsetAsync(S.nb[ctx->cur], 0, (D.ntiles + 1) * sizeof(int32_t), ctx->stream));
     ctx->binned[box][s] = 0;
-    std::vector<int32_t> cell(n), pid(S.stage.id ? n : 0);
-    std::vector<R> dd[3], uu[3];
-    for (int a = 0; a < 3; ++a) { dd[a].resize(n); uu[a].resize(n); }
-    for (int64_t p = 0; p < n; ++p) {
-        int c[3];
-        for (int a = 0; a < 3; ++a) {
-            const int N = D.n[a];
-            double v = std::fmod(x[3 * p + a], (double)N);
-            if (v < 0) v += N;
-            if (v >= N) v -= N;
-            const double f = std::floor(v);
-            R off = (R)(v - f);
-            int ci = (int)f;
-            if (off >= R(1)) { off = R(0); ci += 1; }
-            if (ci >= N) ci -= N;
-            c[a] = ci;
-            dd[a][p] = off;
-            uu[a][p] = (R)u[3 * p + a];
-        }
-        cell[p] = pack_cell(c[0], c[1], c[2]);
-        if (S.stage.id) pid[p] = id ? id[p] : (int32_t)p;
+    // the caller's FP64 values go to the GPU as they are (through the slots of
+    // the copy that the next push overwrites) and are converted there
+    double *dx = reinterpret_cast<double *>(S.buf[ctx->cur ^ 1].rec);
+    const int64_t chunk = (int64_t)(PBuf<R>::bytes(S.slots) / (6 * sizeof(double)));
+    double *du = dx + 3 * chunk;
+    for (int64_t lo = 0; lo < n; lo += chunk) {
+        const int64_t m = std::min(n - lo, chunk);
+        HIPCHK(hipMemcpyAsync(dx, x + 3 * lo, 3 * m * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
+        HIPCHK(hipMemcpyAsync(du, u + 3 * lo, 3 * m * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
+        HIPCHK(launch_particles_in<R>(dev_boxes<R>(ctx), box, s, (int)lo, (int)m, dx, du, id ? 0 : 1, ctx->stream));
     }
-    if (n > 0) {
-        HIPCHK(hipMemcpyAsync(S.stage.cell, cell.data(), n * 4, hipMemcpyHostToDevice, ctx->stream));
-        for (int a = 0; a < 3; ++a) {
-            HIPCHK(hipMemcpyAsync(S.stage.d[a], dd[a].data(), n * sizeof(R), hipMemcpyHostToDevice, ctx->stream));
-            HIPCHK(hipMemcpyAsync(S.stage.u[a], uu[a].data(), n * sizeof(R), hipMemcpyHostToDevice, ctx->stream));
-        }
-        if (S.stage.id) HIPCHK(hipMemcpyAsync(S.stage.id, pid.data(), n * 4, hipMemcpyHostToDevice, ctx->stream));
-    }
+    if (n > 0 && id && S.stage.id)
+        HIPCHK(hipMemcpyAsync(S.stage.id, id, n * sizeof(int32_t), hipMemcpyHostToDevice, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
     ctx->stage_n[box][s] = (int32_t)n;
     ctx->stage_half[box][s] = 0;
@@ -1022,30 +1065,58 @@ int pic_set_particles(pic_ctx *ctx, int box, int species, const double *x, const
                      : set_particles_t<float>(ctx, box, species, x, u, id, n);
 }
 
+// Fields to the host.  Small boxes (all their fields within kPinnedBytes of the
+// arena, FP32 form up to 8736 cells): one copy into the context's pinned buffer,
+// converted from there, since launches and copies cost more than the values
+// (16^3 cells: 31 us; 54 with a copy and a wait for each field).  Larger ones: the FP32
+// form's are converted on the GPU, in the current's array (zero between steps,
+// and cleared again after its use), and copied from there into the caller's
+// arrays; the FP64 form's are copied as they lie.  (64^3 cells: 2.4 ms, most of
+// it the caller's fresh pages; converted by the host, 3.5.)
 template <typename R>
 static int get_fields_t(pic_ctx *ctx, int box, double *e, double *b, double *j)
 {
-    using JT = typename JType<R>::T;
     const BoxDev<R> &D = bdvec<R>(ctx)[box];
-    const size_t n3 = 3 * D.nc;
-    std::vector<R> tmp(n3);
-    if (e) {
-        HIPCHK(hipMemcpyAsync(tmp.data(), D.e, n3 * sizeof(R), hipMemcpyDeviceToHost, ctx->stream));
+    const int64_t n3 = 3 * D.nc;
+    double *scratch = reinterpret_cast<double *>(D.J);
+    const char *first = reinterpret_cast<const char *>(D.e);       // e, b, bn, J lie in this order
+    const size_t span = reinterpret_cast<const char *>(D.J + n3) - first;
+    if (span <= kPinnedBytes) {
+        HIPCHK(hipMemcpyAsync(ctx->pinned, first, span, hipMemcpyDeviceToHost, ctx->stream));
         HIPCHK(hipStreamSynchronize(ctx->stream));
-        for (size_t q = 0; q < n3; ++q) e[q] = (double)tmp[q];
+        auto out = [&](double *to, const auto *field, double scale) {
+            const auto *from = reinterpret_cast<decltype(field)>(ctx->pinned + (reinterpret_cast<const char *>(field) - first));
+            if (to)
+                for (int64_t q = 0; q < n3; ++q) to[q] = (double)from[q] * scale;
+        };
+        out(e, D.e, 1.0);
+        out(b, cur_b(ctx, D), 1.0);
+        out(j, D.J, ctx->fp64 ? 1.0 : std::ldexp(1.0, -kQBits));
+        return PIC_OK;
     }
-    if (b) {
-        HIPCHK(hipMemcpyAsync(tmp.data(), cur_b(ctx, D), n3 * sizeof(R), hipMemcpyDeviceToHost, ctx->stream));
-        HIPCHK(hipStreamSynchronize(ctx->stream));
-        for (size_t q = 0; q < n3; ++q) b[q] = (double)tmp[q];
+    auto out = [&](double *to, const double *from) {
+        return hipMemcpyAsync(to, from, n3 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream);
+    };
+    if constexpr (sizeof(R) == 8) {
+        if (e) HIPCHK(out(e, D.e));
+        if (b) HIPCHK(out(b, cur_b(ctx, D)));
+        if (j) HIPCHK(out(j, D.J));
+    } else {
+        if (j) {
+            HIPCHK(launch_fields_out(D.J, std::ldexp(1.0, -kQBits), n3, scratch, ctx->stream));   // in place
+            HIPCHK(out(j, scratch));
+        }
+        if (e) {
+            HIPCHK(launch_fields_out(D.e, 1.0, n3, scratch, ctx->stream));
+            HIPCHK(out(e, scratch));
+        }
+        if (b) {
+            HIPCHK(launch_fields_out(cur_b(ctx, D), 1.0, n3, scratch, ctx->stream));
+            HIPCHK(out(b, scratch));
+        }
+        if (e || b || j) HIPCHK(launch_zero(scratch, n3, ctx->stream));
     }
-    if (j) {
-        std::vector<JT> jt(n3);
-        HIPCHK(hipMemcpyAsync(jt.data(), D.J, n3 * sizeof(JT), hipMemcpyDeviceToHost, ctx->stream));
-        HIPCHK(hipStreamSynchronize(ctx->stream));
-        const double sc = ctx->fp64 ? 1.0 : std::ldexp(1.0, -kQBits);
-        for (size_t q = 0; q < n3; ++q) j[q] = (double)jt[q] * sc;
-    }
+    HIPCHK(hipStreamSynchronize(ctx->stream));
     return PIC_OK;
 }
 
@@ -1053,36 +1124,25 @@ int pic_get_fields(pic_ctx *ctx, int box, double *e, double *b, double *j)
 {
     int rc = check_box(ctx, box);
     if (rc) return rc;
-    HIPCHK(hipStreamSynchronize(ctx->stream));
     return ctx->fp64 ? get_fields_t<double>(ctx, box, e, b, j) : get_fields_t<float>(ctx, box, e, b, j);
 }
 
+// Fields from the host, converted on the GPU through the current's array (zero
+// between steps, and cleared again).
 template <typename R>
 static int set_fields_t(pic_ctx *ctx, int box, const double *e, const double *b)
 {
     const BoxDev<R> &D = bdvec<R>(ctx)[box];
-    const size_t n3 = 3 * D.nc;
-    std::vector<R> tmp(n3);
-    // with conducting walls the given fields take the conductor's condition on
-    // the wall plane (index 0 along the wall axis): no tangential e, no
-    // normal b (App. A.4)
-    auto on_wall = [&](size_t p) {
-        const int64_t i = (int64_t)(p % D.n[0]), j = (int64_t)((p / D.n[0]) % D.n[1]),
-                      k = (int64_t)(p / ((size_t)D.n[0] * D.n[1]));
-        return D.wall >= 0 && (D.wall == 0 ? i : (D.wall == 1 ? j : k)) == 0;
+    const int64_t n3 = 3 * D.nc;
+    double *scratch = reinterpret_cast<double *>(D.J);
+    auto in = [&](const double *from, R *to, int is_b) -> hipError_t {
+        const hipError_t rc = hipMemcpyAsync(scratch, from, n3 * sizeof(double), hipMemcpyHostToDevice, ctx->stream);
+        return rc != hipSuccess ? rc : launch_fields_in<R>(scratch, D.n, D.wall, is_b, to, ctx->stream);
     };
-    if (e) {
-        for (size_t q = 0; q < n3; ++q)
-            tmp[q] = ((int)(q / D.nc) != D.wall && on_wall(q % D.nc)) ? R(0) : (R)e[q];
-        HIPCHK(hipMemcpyAsync(D.e, tmp.data(), n3 * sizeof(R), hipMemcpyHostToDevice, ctx->stream));
-        HIPCHK(hipStreamSynchronize(ctx->stream));
-    }
-    if (b) {
-        for (size_t q = 0; q < n3; ++q)
-            tmp[q] = ((int)(q / D.nc) == D.wall && on_wall(q % D.nc)) ? R(0) : (R)b[q];
-        HIPCHK(hipMemcpyAsync(cur_b(ctx, D), tmp.data(), n3 * sizeof(R), hipMemcpyHostToDevice, ctx->stream));
-        HIPCHK(hipStreamSynchronize(ctx->stream));
-    }
+    if (e) HIPCHK(in(e, D.e, 0));
+    if (b) HIPCHK(in(b, cur_b(ctx, D), 1));
+    if (e || b) HIPCHK(launch_zero(scratch, n3, ctx->stream));
+    HIPCHK(hipStreamSynchronize(ctx->stream));
     return PIC_OK;
 }
 
@@ -1090,7 +1150,6 @@ int pic_set_fields(pic_ctx *ctx, int box, const double *e, const double *b)
 {
     int rc = check_box(ctx, box);
     if (rc) return rc;
-    HIPCHK(hipStreamSynchronize(ctx->stream));
     return ctx->fp64 ? set_fields_t<double>(ctx, box, e, b) : set_fields_t<float>(ctx, box, e, b);
 }
 

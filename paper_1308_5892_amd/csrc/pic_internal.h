@@ -236,6 +236,51 @@ __host__ __device__ inline void tile_origin(const BoxDev<R> &B, int T, int o[3])
     o[2] = (r / B.ntile[1]) << B.tshift[2];
 }
 
+// The particles of tile T in copy c: the A range then the clamped B range.
+struct TileRanges {
+    int start, na, bs, n;
+    __device__ int slot(int q) const { return start + (q < na ? q : bs + (q - na)); }
+};
+
+template <typename R>
+__device__ inline TileRanges tile_ranges(const SpeciesDev<R> &S, int c, int T)
+{
+    TileRanges r;
+    r.start = S.seg_start[c][T];
+    r.na = S.na[c][T];
+    r.bs = S.bs[c][T];
+    r.n = r.na + max(0, min(S.nb[c][T], S.seg_cap[c][T] - r.bs));
+    return r;
+}
+
+// The overflow region of copy c as a range.
+template <typename R>
+__device__ inline TileRanges overflow_range(const BoxDev<R> &B, const SpeciesDev<R> &S, int c)
+{
+    TileRanges r;
+    r.start = S.seg_start[c][B.ntiles];
+    r.na = min(S.nb[c][B.ntiles], S.ovf_cap);
+    r.bs = 0;
+    r.n = r.na;
+    return r;
+}
+
+// The particles of a work item in copy c: a tile's A and B ranges (one block
+// striding), or the overflow region (kOvfBlocks blocks striding).
+template <typename R>
+__device__ inline TileRanges item_range(const BoxDev<R> &B, const SpeciesDev<R> &S, int c, int tile, int &first,
+                                        int &stride)
+{
+    if (tile >= 0) {
+        first = threadIdx.x;
+        stride = kBlock;
+        return tile_ranges(S, c, tile);
+    }
+    first = (-1 - tile) * kBlock + threadIdx.x;
+    stride = kBlock * kOvfBlocks;
+    return overflow_range(B, S, c);
+}
+
 // cell blocks of the field kernels: (box, first cell) of kBlock cells
 struct CellBlock {
     int32_t box;
@@ -313,6 +358,22 @@ hipError_t launch_repack(const BoxDev<R> *boxes, int nboxes, const Item *items, 
 template <typename R>
 hipError_t launch_diag(const BoxDev<R> *boxes, int box, int64_t nc, const Item *items, int nitems,
                        const StepConst<R> &C, const DiagBuf &out, int hist_len, hipStream_t st);
+// copies to and from the host (pic_io.hip)
+template <typename SRC> hipError_t launch_fields_out(const SRC *src, double scale, int64_t n, double *dst, hipStream_t st);
+template <typename R>
+hipError_t launch_fields_in(const double *src, const int n[3], int wall, int is_b, R *dst, hipStream_t st);
+template <typename R>
+hipError_t launch_particle_offsets(const BoxDev<R> *boxes, int box, int s, int cur, int32_t *info, hipStream_t st);
+template <typename R>
+hipError_t launch_particle_ids(const BoxDev<R> *boxes, const Item *items, int nitems, int s, int cur, int total,
+                               uint32_t *seen, int32_t *info, hipStream_t st);
+template <typename R>
+hipError_t launch_particles_out(const BoxDev<R> *boxes, const Item *items, int nitems, int s, int cur, int by_id, int lo,
+                                int hi, double *x, double *u, int32_t *ids, hipStream_t st);
+template <typename R>
+hipError_t launch_particles_in(const BoxDev<R> *boxes, int box, int s, int lo, int n, const double *x, const double *u,
+                               int own_ids, hipStream_t st);
+hipError_t launch_zero(void *p, int64_t words, hipStream_t st);   // 8-byte words
 // device address of the static diagnostics scratch of the current device:
 // set up once per device (pic_init), then read
 hipError_t diag_scratch_setup();

@@ -298,35 +298,6 @@ __device__ inline void store_particle(const BoxDev<R> &B, const SpeciesDev<R> &S
     if (at >= 0) write_particle(S.buf[dst], at, at >= S.slots - S.ovf_cap, cell, local_code(B, cell), d, u, id);
 }
 
-// The particles of tile T in copy c: the A range then the clamped B range.
-struct TileRanges {
-    int start, na, bs, n;
-    __device__ int slot(int q) const { return start + (q < na ? q : bs + (q - na)); }
-};
-
-template <typename R>
-__device__ inline TileRanges tile_ranges(const SpeciesDev<R> &S, int c, int T)
-{
-    TileRanges r;
-    r.start = S.seg_start[c][T];
-    r.na = S.na[c][T];
-    r.bs = S.bs[c][T];
-    r.n = r.na + max(0, min(S.nb[c][T], S.seg_cap[c][T] - r.bs));
-    return r;
-}
-
-// The overflow region of copy c as a range.
-template <typename R>
-__device__ inline TileRanges overflow_range(const BoxDev<R> &B, const SpeciesDev<R> &S, int c)
-{
-    TileRanges r;
-    r.start = S.seg_start[c][B.ntiles];
-    r.na = min(S.nb[c][B.ntiles], S.ovf_cap);
-    r.bs = 0;
-    r.n = r.na;
-    return r;
-}
-
 // Offset of x in its cell, x - floor(x), kept below 1: an x a hair below a
 // node plane, whose difference would round up to 1, stays in the lower cell
 // at the largest offset below 1 (one v_fract_f32, which clamps so).
@@ -1995,22 +1966,6 @@ __global__ void __launch_bounds__(kBlock) clear_current_kernel(const BoxDev<R> *
 
 // ------------------------------------------------------ counting-sort repack
 
-// The particles of a work item in copy c: a tile's A and B ranges (one block
-// striding), or the overflow region (kOvfBlocks blocks striding).
-template <typename R>
-__device__ inline TileRanges item_range(const BoxDev<R> &B, const SpeciesDev<R> &S, int c, int tile, int &first,
-                                        int &stride)
-{
-    if (tile >= 0) {
-        first = threadIdx.x;
-        stride = kBlock;
-        return tile_ranges(S, c, tile);
-    }
-    first = (-1 - tile) * kBlock + threadIdx.x;
-    stride = kBlock * kOvfBlocks;
-    return overflow_range(B, S, c);
-}
-
 // Tile counts for the repack: a tile's ranges hold only particles of that
 // tile, so they count as a whole; overflow particles one by one.
 template <typename R>
@@ -2595,6 +2550,13 @@ __global__ void __launch_bounds__(kBlock) zero_words_kernel(uint64_t *__restrict
 {
     PIC_GLOBAL uint64_t *q = (PIC_GLOBAL uint64_t *)p;
     for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < n; t += (int64_t)gridDim.x * kBlock) q[t] = 0;
+}
+
+hipError_t launch_zero(void *p, int64_t words, hipStream_t st)
+{
+    hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)std::min<int64_t>(1024, (words + kBlock - 1) / kBlock)),
+                       dim3(kBlock), 0, st, (uint64_t *)p, words);
+    return hipGetLastError();
 }
 
 template <typename R>
