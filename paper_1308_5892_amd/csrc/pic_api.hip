@@ -10,6 +10,7 @@
 #include <new>
 #include <numeric>
 #include <string>
+#include <thread>
 #include <vector>
 
 #define PIC_HOST_ONLY_TU   // no kernels here: descriptor pointers stay generic
@@ -233,7 +234,7 @@ using namespace pic;
 // Overflow watch: after every push the last block of the e update writes the
 // fill of the fullest overflow region (thousandths of its capacity) straight
 // into a slot of coherent pinned host memory; pic_step reads it kWatchLag steps later
-// (waiting for that step only, so the stream stays kWatchLag steps ahead) and
+// (waiting for that report only, so the stream stays kWatchLag steps ahead) and
 // repacks at once when the fill is above kWatchLimit, instead of letting the
 // overflow region - swept by the slow path - fill up or lose particles.
 constexpr int kWatch = 4, kWatchLag = 2;
@@ -273,11 +274,9 @@ struct pic_ctx {
     int timing = 0;                    // 0 off, 1 every launch kind, 2 the push only
     std::vector<std::pair<hipEvent_t, hipEvent_t>> ev[3];
     std::vector<hipEvent_t> ev_pool;
-    uint32_t *watch_host = nullptr;          // pinned, coherent, kWatch slots
-    uint32_t *watch_dev = nullptr;           // the same slots as the device addresses them
+    uint64_t *watch_host = nullptr;          // pinned, coherent, kWatch slots
+    uint64_t *watch_dev = nullptr;           // the same slots as the device addresses them
     char *pinned = nullptr;                  // kPinnedBytes behind the slots
-    hipEvent_t watch_ev[kWatch] = {};
-    int64_t watch_step[kWatch] = {-1, -1, -1, -1};
     int64_t last_repack = 0;
     int64_t early_repacks = 0;
     ~pic_ctx()
@@ -285,8 +284,6 @@ struct pic_ctx {
         for (auto &v : ev)
             for (auto &p : v) { hipEventDestroy(p.first); hipEventDestroy(p.second); }
         for (auto e : ev_pool) hipEventDestroy(e);
-        for (auto e : watch_ev)
-            if (e) hipEventDestroy(e);
         if (watch_host) hipHostFree(watch_host);
     }
 };
@@ -629,11 +626,6 @@ int pic_init(const pic_config *cfg, void *dev_arena, size_t bytes, void *hip_str
         delete ctx;
         return PIC_EDEVICE;
     }
-    for (auto &e : ctx->watch_ev)
-        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
-            delete ctx;
-            return PIC_EDEVICE;
-        }
     // device address of pic_diag_noalloc's static scratch on this device (once per device)
     if (diag_scratch_setup() != hipSuccess) {
         delete ctx;
@@ -697,17 +689,48 @@ int pic_sync(pic_ctx *ctx)
     return PIC_OK;
 }
 
+// The overflow watch of step `look` (at least one step behind the last one
+// enqueued).  The host polls the slot that the step's e update stores to: an
+// event per step in its place put a barrier packet between the e update and
+// the next push, 4.5 us of every step (a sixth of the step of a 16^3 box).  A
+// stream that has run dry without the report, or failed, ends the wait.
+static int wait_watch(pic_ctx *ctx, int64_t look, uint32_t *fill)
+{
+    const uint64_t *slot = ctx->watch_host + look % kWatch;
+    for (int64_t spin = 0;; ++spin) {
+        const uint64_t v = __atomic_load_n(slot, __ATOMIC_ACQUIRE);
+        if ((uint32_t)(v >> 32) == (uint32_t)look) {
+            *fill = (uint32_t)v;
+            return PIC_OK;
+        }
+        if (spin < 4096) {
+            __builtin_ia32_pause();
+            continue;
+        }
+        std::this_thread::yield();
+        if (spin % 4096) continue;
+        const hipError_t e = hipStreamQuery(ctx->stream);
+        if (e == hipErrorNotReady) continue;
+        if (e != hipSuccess || (uint32_t)(__atomic_load_n(slot, __ATOMIC_ACQUIRE) >> 32) != (uint32_t)look) {
+            ctx->err = e != hipSuccess ? std::string("stream: ") + hipGetErrorString(e) : "a step left no overflow report";
+            return PIC_EDEVICE;
+        }
+    }
+}
+
 template <typename R>
 static int step_t(pic_ctx *ctx, int n)
 {
     for (int i = 0; i < n; ++i) {
         // early repack when the overflow watch of kWatchLag steps ago says so
         const int64_t look = ctx->step - kWatchLag;
-        if (look > ctx->last_repack && ctx->watch_step[look % kWatch] == look) {
-            HIPCHK(hipEventSynchronize(ctx->watch_ev[look % kWatch]));
-            if (ctx->watch_host[look % kWatch] > kWatchLimit) {
+        if (look > ctx->last_repack) {
+            uint32_t fill = 0;
+            int rc = wait_watch(ctx, look, &fill);
+            if (rc) return rc;
+            if (fill > kWatchLimit) {
                 mark(ctx, 2, true);
-                int rc = merge_t<R>(ctx, true);
+                rc = merge_t<R>(ctx, true);
                 mark(ctx, 2, false);
                 if (rc) return rc;
                 ctx->last_repack = ctx->step;
@@ -727,13 +750,12 @@ static int step_t(pic_ctx *ctx, int n)
         // just written, into the host slot of the step about to complete
         const int w = (int)((ctx->step + 1) % kWatch);
         HIPCHK(launch_fields<R>(dev_boxes<R>(ctx), ctx->L.cblocks, ctx->L.n_cblocks, (R)ctx->cfg.dt,
-                                ctx->cfg.n_species, C.filter, ctx->cur, ctx->cfg.n_boxes, ctx->watch_dev + w,
+                                ctx->cfg.n_species, C.filter, ctx->cur, ctx->cfg.n_boxes,
+                                Watch{ctx->watch_dev + w, (uint32_t)(ctx->step + 1)},
                                 ctx->stream));
         mark(ctx, 1, false);
         ctx->cur ^= 1;
         ctx->step += 1;
-        HIPCHK(hipEventRecord(ctx->watch_ev[w], ctx->stream));
-        ctx->watch_step[w] = ctx->step;
         if (ctx->cfg.sort_interval > 0 && ctx->step % ctx->cfg.sort_interval == 0) {
             mark(ctx, 2, true);
             int rc = merge_t<R>(ctx, true);

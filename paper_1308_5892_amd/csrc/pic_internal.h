@@ -341,6 +341,14 @@ static_assert(kAccLen * sizeof(double) % 256 == 0, "rho follows acc in 256-byte 
 // size of the static scratch of pic_diag_noalloc (per GPU)
 constexpr size_t kDiagScratchBytes = size_t(32) << 20;
 
+// Where a step's overflow watch goes: 8 bytes of coherent host memory, the
+// step's number in the upper half and the fill in the lower, stored at once, so
+// that the host can tell a step's report from an older one by itself.
+struct Watch {
+    uint64_t *slot;
+    uint32_t step;
+};
+
 // launchers (pic_kernels.hip, pic_loader.hip)
 template <typename R> size_t push_lds_bytes(int t0, int t1, int t2);
 template <typename R>
@@ -348,7 +356,7 @@ hipError_t launch_push(const BoxDev<R> *boxes, const Item *items, int nitems, si
                        int fixed444, int walls, int faraday4, hipStream_t st);
 template <typename R>
 hipError_t launch_fields(const BoxDev<R> *boxes, const CellBlock *blocks, int nblocks, R dt, int nsp, int filter,
-                         int clear_copy, int nboxes, uint32_t *watch, hipStream_t st);
+                         int clear_copy, int nboxes, Watch watch, hipStream_t st);
 template <typename R>
 hipError_t launch_advance_b(const BoxDev<R> *boxes, const CellBlock *blocks, int nblocks, R h, hipStream_t st);
 template <typename R>

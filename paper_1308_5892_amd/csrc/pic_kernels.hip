@@ -1772,7 +1772,7 @@ __device__ inline void next_layout(const BoxDev<R> &B, int nsp, int old, int t)
 // 1024 particles (the load its sweep blocks take in four rounds).
 template <typename R>
 __device__ void overflow_watch_block(const BoxDev<R> *__restrict__ boxes, int nboxes, int nsp, int copy,
-                                     uint32_t *__restrict__ out)
+                                     const Watch &out)
 {
     __shared__ unsigned int best;
 
@@ -1791,7 +1791,8 @@ __device__ void overflow_watch_block(const BoxDev<R> *__restrict__ boxes, int nb
     }
     atomicMax(&best, m);
     __syncthreads();
-    if (threadIdx.x == 0) *out = best;
+    if (threadIdx.x == 0)
+        __hip_atomic_store(out.slot, ((uint64_t)out.step << 32) | best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Book-keeping after a push, by the first field kernel that follows it: the
@@ -1800,11 +1801,11 @@ __device__ void overflow_watch_block(const BoxDev<R> *__restrict__ boxes, int nb
 // written); the whole last block reaches the watch's barriers.
 template <typename R>
 __device__ inline void after_push(const BoxDev<R> *__restrict__ boxes, const BoxDev<R> &B, int64_t p, int nsp,
-                                  int old, int nboxes, uint32_t *__restrict__ watch)
+                                  int old, int nboxes, Watch watch)
 {
     if (p < B.ntiles) next_layout(B, nsp, old, (int)p);
     if (p == 0) next_layout(B, nsp, old, B.ntiles);
-    if (watch && blockIdx.x == gridDim.x - 1) overflow_watch_block(boxes, nboxes, nsp, old ^ 1, watch);
+    if (watch.slot && blockIdx.x == gridDim.x - 1) overflow_watch_block(boxes, nboxes, nsp, old ^ 1, watch);
 }
 
 // Coordinates of cell p of a box with edges n0, n1 (p < n0 n1 n2 <= 2^32, so
@@ -1857,7 +1858,7 @@ __global__ void __launch_bounds__(kBlock) advance_b_kernel(const BoxDev<R> *__re
 template <typename R>
 __global__ void __launch_bounds__(kBlock) advance_e_kernel(const BoxDev<R> *__restrict__ boxes,
                                                            const CellBlock *__restrict__ blocks, R dt, int nsp,
-                                                           int old, int nboxes, uint32_t *__restrict__ watch)
+                                                           int old, int nboxes, Watch watch)
 {
     using JT = typename JType<R>::T;
     const CellBlock cb = blocks[blockIdx.x];
@@ -1923,7 +1924,7 @@ template <typename R>
 __global__ void __launch_bounds__(kBlock) advance_e_smoothed_kernel(const BoxDev<R> *__restrict__ boxes,
                                                                     const CellBlock *__restrict__ blocks, R dt,
                                                                     int nsp, int old, int nboxes,
-                                                                    uint32_t *__restrict__ watch)
+                                                                    Watch watch)
 {
     using JT = typename JType<R>::T;
     const CellBlock cb = blocks[blockIdx.x];
@@ -2488,7 +2489,7 @@ hipError_t launch_push(const BoxDev<R> *boxes, const Item *items, int nitems, si
 
 template <typename R>
 hipError_t launch_fields(const BoxDev<R> *boxes, const CellBlock *blocks, int nblocks, R dt, int nsp, int filter,
-                         int clear_copy, int nboxes, uint32_t *watch, hipStream_t st)
+                         int clear_copy, int nboxes, Watch watch, hipStream_t st)
 {
     if (filter) {
         hipLaunchKernelGGL(advance_e_smoothed_kernel<R>, dim3(nblocks), dim3(kBlock), 0, st, boxes, blocks, dt, nsp,
@@ -2785,7 +2786,7 @@ hipError_t launch_spectrum(const BoxDev<R> *boxes, int box, const int n[3], int 
     template hipError_t launch_push<R>(const BoxDev<R> *, const Item *, int, size_t, const StepConst<R> &,   \
                                        int, int, int, hipStream_t);                                           \
     template hipError_t launch_fields<R>(const BoxDev<R> *, const CellBlock *, int, R, int, int, int, int,     \
-                                         uint32_t *, hipStream_t);                                                        \
+                                         Watch, hipStream_t);                                                        \
     template hipError_t launch_advance_b<R>(const BoxDev<R> *, const CellBlock *, int, R, hipStream_t);       \
     template hipError_t launch_repack<R>(const BoxDev<R> *, int, const Item *, int, const StageItem *, int,    \
                                          int, const uint32_t *, size_t, int, const StepConst<R> &, hipStream_t); \
