@@ -267,6 +267,7 @@ struct pic_ctx {
     size_t lds_bytes = 0;
     bool fixed444 = false;             // every tile 4x4x4 and every particle copy below 4 GiB: the fixed-shape push kernel
     bool walls = false;                // some box has conducting walls
+    int wide = 0;                      // few tiles: the push with this many threads per tile
     bool pending = false;
     uint32_t flags_seen = 0;
     std::string err;
@@ -555,7 +556,13 @@ static int init_t(pic_ctx *ctx)
     ctx->lds_bytes = lds;
     ctx->fixed444 = all444;
     ctx->walls = false;
-    for (auto &H : ctx->bh) ctx->walls = ctx->walls || H.cfg.walls != 0;
+    int ntiles = 0;
+    for (auto &H : ctx->bh) {
+        ctx->walls = ctx->walls || H.cfg.walls != 0;
+        ntiles += std::min(H.ntiles, kWideTiles + 1);
+        if (ntiles > kWideTiles) ntiles = kWideTiles + 1;
+    }
+    ctx->wide = ctx->fixed444 && !ctx->walls ? wide_threads<R>(ntiles) : 0;
     HIPCHK(hipStreamSynchronize(ctx->stream));
     // initial segment layout: an empty repack
     return merge_t<R>(ctx, true);
@@ -739,9 +746,10 @@ static int step_t(pic_ctx *ctx, int n)
         }
         StepConst<R> C = step_const<R>(ctx);
         mark(ctx, 0, true);
-        HIPCHK(launch_push<R>(dev_boxes<R>(ctx), ctx->L.items_push, ctx->n_push, ctx->lds_bytes, C,
+        HIPCHK(launch_push<R>(dev_boxes<R>(ctx), ctx->L.items_push, ctx->n_push,
+                              ctx->wide ? wide_lds_bytes<R>(ctx->wide) : ctx->lds_bytes, C,
                               ctx->fixed444 ? 1 : 0, ctx->walls ? 1 : 0, (ctx->cfg.flags & PIC_FARADAY4) ? 1 : 0,
-                              ctx->stream));
+                              ctx->wide, ctx->stream));
         mark(ctx, 0, false);
         // the push wrote b^{t+dt/2} into the other b buffer: it is the current one now
         ctx->bpar ^= 1;

@@ -42,6 +42,14 @@ namespace pic {
 constexpr int kMaxSpecies = PIC_MAX_SPECIES;
 constexpr int kOvfBlocks = 16;     // blocks per box sweeping the overflow region
 constexpr int kBlock = 256;        // threads per block of the particle kernels
+// threads per block of the push where tiles are few (0: kBlock): up to two tiles
+// per CU, and up to one in the FP32 form (wide_push_kernel has the times)
+constexpr int kWideTiles = 512;
+template <typename R>
+constexpr int wide_threads(int tiles)
+{
+    return tiles > kWideTiles ? 0 : (tiles <= kWideTiles / 2 && sizeof(R) == 4 ? 1024 : 512);
+}
 constexpr int kQBits = 31;         // fractional bits of the fixed-point current
 
 __host__ __device__ inline int32_t pack_cell(int ix, int iy, int iz)
@@ -351,9 +359,10 @@ struct Watch {
 
 // launchers (pic_kernels.hip, pic_loader.hip)
 template <typename R> size_t push_lds_bytes(int t0, int t1, int t2);
+template <typename R> size_t wide_lds_bytes(int threads);   // of a wide_push_kernel block (4x4x4 tiles)
 template <typename R>
 hipError_t launch_push(const BoxDev<R> *boxes, const Item *items, int nitems, size_t lds, const StepConst<R> &C,
-                       int fixed444, int walls, int faraday4, hipStream_t st);
+                       int fixed444, int walls, int faraday4, int wide, hipStream_t st);
 template <typename R>
 hipError_t launch_fields(const BoxDev<R> *boxes, const CellBlock *blocks, int nblocks, R dt, int nsp, int filter,
                          int clear_copy, int nboxes, Watch watch, hipStream_t st);

@@ -368,9 +368,9 @@ template <> struct QCap<double> { static constexpr int value = 64; };
 constexpr int kWaves = kBlock / 64;
 
 template <typename R>
-__host__ __device__ inline size_t queue_bytes()
+__host__ __device__ inline size_t queue_bytes(int waves)
 {
-    return (size_t)kWaves * QCap<R>::value * (2 * sizeof(int32_t) + 6 * sizeof(R));
+    return (size_t)waves * QCap<R>::value * (2 * sizeof(int32_t) + 6 * sizeof(R));
 }
 
 // Bytes of dynamic LDS for a tile with edges (t0, t1, t2): the trilinear
@@ -393,13 +393,13 @@ struct TileLds {
 };
 
 template <typename R>
-__host__ __device__ inline TileLds tile_lds(int t0, int t1, int t2)
+__host__ __device__ inline TileLds tile_lds(int t0, int t1, int t2, int waves = kWaves)
 {
     const size_t nc = (size_t)t0 * t1 * t2;
     const size_t nn = (size_t)(t0 + 1) * (t1 + 1) * (t2 + 1);
     const size_t jn = (size_t)(t0 + 3) * (t1 + 3) * (t2 + 3);
     const size_t bn = (size_t)(t0 + 2) * (t1 + 2) * (t2 + 2);
-    const size_t raw = 3 * (jn + bn) * sizeof(R), q = queue_bytes<R>();
+    const size_t raw = 3 * (jn + bn) * sizeof(R), q = queue_bytes<R>(waves);
     const size_t nodes = 6 * nn * sizeof(R), jb = 3 * jn * sizeof(typename JType<R>::T);
     TileLds L;
     L.coef = (nc * kCoef * sizeof(R) + 15) & ~size_t(15);
@@ -857,7 +857,7 @@ struct TileGrid {
 // staged() is called by every thread once the raw fields are staged and says
 // whether the tile has particles; without any the set-up ends after b, and
 // its result is passed on.
-template <typename R, int FIX, int WALLS, int F4, bool STEP, typename Staged>
+template <typename R, int FIX, int WALLS, int F4, bool STEP, int NT, typename Staged>
 __device__ __forceinline__ bool tile_coefs(const BoxDev<R> &B, const TileGeom<R> &g, const TileGrid<R> &gidx, R dt,
                                            R *coef, R *re, R *rb, R *node, Staged &&staged)
 {
@@ -872,14 +872,14 @@ __device__ __forceinline__ bool tile_coefs(const BoxDev<R> &B, const TileGeom<R>
     const int tsx = FIX ? 2 : B.tshift[0], tsxy = FIX ? 4 : B.tshift[0] + B.tshift[1];
 
     // 1. stage e^t and b^{t-dt/2} of the tile and its halo
-    for (int q = tid; q < g.JN; q += kBlock) {
+    for (int q = tid; q < g.JN; q += NT) {
         const int jk = div_small(q, mJX), i = q - jk * JX;
         const int k = div_small(jk, mJY), j = jk - k * g.JY;
         const int64_t gp = gidx(i, j, k);
 #pragma unroll
         for (int c = 0; c < 3; ++c) re[c * g.JN + q] = B.e[c * B.nc + gp];
     }
-    for (int q = tid; q < g.BN; q += kBlock) {
+    for (int q = tid; q < g.BN; q += NT) {
         const int jk = div_small(q, mBX), i = q - jk * BX;
         const int k = div_small(jk, mBY), j = jk - k * g.BY;
         const int64_t gp = gidx(i, j, k);
@@ -915,7 +915,7 @@ __device__ __forceinline__ bool tile_coefs(const BoxDev<R> &B, const TileGeom<R>
         // the fourth-order curl reaches two cells out, past the staged halo:
         // b^t from HBM, exactly as the HBM path forms it (staging the wider e
         // instead changed the push by 0.2 %)
-        for (int q = tid; q < g.BN; q += kBlock) {
+        for (int q = tid; q < g.BN; q += NT) {
             const int jk = div_small(q, mBX), i = q - jk * BX;
             const int k = div_small(jk, mBY), j = jk - k * g.BY;
             const int gi = g.o[0] - 1 + i, gj = g.o[1] - 1 + j, gk = g.o[2] - 1 + k;
@@ -935,7 +935,7 @@ __device__ __forceinline__ bool tile_coefs(const BoxDev<R> &B, const TileGeom<R>
         }
     } else {
         const R *ex = re, *ey = re + g.JN, *ez = re + 2 * g.JN;
-        for (int q = tid; q < g.BN; q += kBlock) {
+        for (int q = tid; q < g.BN; q += NT) {
             const int jk = div_small(q, mBX), i = q - jk * BX;
             const int k = div_small(jk, mBY), j = jk - k * g.BY;
             const int p = i + JX * j + JXY * k;
@@ -959,7 +959,7 @@ __device__ __forceinline__ bool tile_coefs(const BoxDev<R> &B, const TileGeom<R>
     {
         const R *ex = re, *ey = re + g.JN, *ez = re + 2 * g.JN;
         const R *bx = rb, *by = rb + g.BN, *bz = rb + 2 * g.BN;
-        for (int q = tid; q < g.NN; q += kBlock) {
+        for (int q = tid; q < g.NN; q += NT) {
             const int jk = div_small(q, mNX), i = q - jk * NX;
             const int k = div_small(jk, mNY), j = jk - k * g.NY;
             // raw coordinates of node (i,j,k) are (i+1, j+1, k+1)
@@ -982,7 +982,7 @@ __device__ __forceinline__ bool tile_coefs(const BoxDev<R> &B, const TileGeom<R>
     {
         const int ncell = g.ext[0] * g.ext[1] * g.ext[2];
         const int mEX = 65536 / g.ext[0] + 1, mEY = 65536 / g.ext[1] + 1;
-        for (int q = tid; q < ncell; q += kBlock) {
+        for (int q = tid; q < ncell; q += NT) {
             const int jk = div_small(q, mEX), i = q - jk * g.ext[0];
             const int k = div_small(jk, mEY), j = jk - k * g.ext[1];
             R *cf = coef + kCoef * (i | (j << tsx) | (k << tsxy));
@@ -1000,7 +1000,7 @@ __device__ __forceinline__ bool tile_coefs(const BoxDev<R> &B, const TileGeom<R>
 }
 
 // Overflow sweep: same physics, fields from HBM, current by global atomics.
-template <typename R, int WALLS, int F4>
+template <typename R, int WALLS, int F4, int NT>
 __device__ void push_overflow(const BoxDev<R> &B, int kblk, const StepConst<R> &C)
 {
     using JT = typename JType<R>::T;
@@ -1013,7 +1013,7 @@ __device__ void push_overflow(const BoxDev<R> &B, int kblk, const StepConst<R> &
         const PBuf<R> &P = S.buf[C.cur];
         const R hk = R(0.5) * C.kq[s] * C.dt;
         const R scale = -C.qs[s] * qscale_bits<R>();
-        for (int pb = kblk * kBlock; pb < n; pb += kBlock * kOvfBlocks) {
+        for (int pb = kblk * NT; pb < n; pb += NT * kOvfBlocks) {
             const int p = pb + (int)threadIdx.x;
             const bool valid = p < n;
             const int idx = start + (valid ? p : 0);
@@ -1066,13 +1066,10 @@ __device__ void push_overflow(const BoxDev<R> &B, int kblk, const StepConst<R> &
     }
 }
 
-// FP32 form: four waves per SIMD (at most 128 VGPRs), the occupancy that
-// hides the latency of the LDS gather and of the particle loads best on
-// gfx950.  FP64 form: three (at most 168 VGPRs; with its 64-entry queues a
-// 4x4x4 block's LDS allows three blocks per CU as well).
-template <typename R, int FIX, int WALLS, int F4>
-__global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const BoxDev<R> *__restrict__ boxes,
-                                                      const Item *__restrict__ items, StepConst<R> C)
+// The push of one work item by a block of NT threads.
+template <typename R, int FIX, int WALLS, int F4, int NT>
+__device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, const Item *__restrict__ items,
+                                           const StepConst<R> &C)
 {
     using JT = typename JType<R>::T;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1080,7 +1077,7 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
     if (it.box < 0) return;                       // padding of the push order
     const BoxDev<R> &B = boxes[it.box];
     if (it.tile < 0) {
-        push_overflow<R, WALLS, F4>(B, -1 - it.tile, C);
+        push_overflow<R, WALLS, F4, NT>(B, -1 - it.tile, C);
         return;
     }
     const int T = it.tile;
@@ -1114,7 +1111,9 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
     // raw b, node fields} (set-up) and the tile current (particle loop)
     const int tsx = FIX ? 2 : B.tshift[0], tsxy = FIX ? 4 : B.tshift[0] + B.tshift[1];
     const int tsz = FIX ? 2 : B.tshift[2];
-    const TileLds lds = FIX ? tile_lds<R>(4, 4, 4) : tile_lds<R>(1 << B.tshift[0], 1 << B.tshift[1], 1 << B.tshift[2]);
+    constexpr int kWaves = NT / 64;
+    const TileLds lds = FIX ? tile_lds<R>(4, 4, 4, kWaves)
+                            : tile_lds<R>(1 << B.tshift[0], 1 << B.tshift[1], 1 << B.tshift[2], kWaves);
     R *coef = reinterpret_cast<R *>(smem);
     unsigned char *qmem = smem + lds.coef;
     unsigned char *uni = qmem + lds.stage;
@@ -1184,7 +1183,7 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
         return s;
     };
     int s0 = 0;
-    const bool any = tile_coefs<R, FIX, WALLS, F4, true>(B, g, grid, C.dt, coef, re, rb, node, [&]() {
+    const bool any = tile_coefs<R, FIX, WALLS, F4, true, NT>(B, g, grid, C.dt, coef, re, rb, node, [&]() {
         s0 = next_species(-1);
         if (s0 < C.nsp) fetch_particle(B.sp[s0].buf[C.cur], ranges(s0), tid);
         return s0 < C.nsp;
@@ -1193,7 +1192,7 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
     // the other copy is zero already): two thirds of the tiles of a 796 x 632 x 4
     // Harris sheet, whose push takes 0.515 ms with this and 0.548 without
     if (!any) return;
-    for (int q = tid; q < 3 * g.JN; q += kBlock) jl[q] = JT(0);
+    for (int q = tid; q < 3 * g.JN; q += NT) jl[q] = JT(0);
     __syncthreads();
 
     // 5. particles of every species: gather, push, move, deposit, re-bin
@@ -1302,7 +1301,7 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
             const int id = nx_id;
             const R d[3] = {nx_d[0], nx_d[1], nx_d[2]};
             R u[3] = {nx_u[0], nx_u[1], nx_u[2]};
-            int ns = s, npb = pb + kBlock;
+            int ns = s, npb = pb + NT;
             if (npb >= src.n) {
                 ns = next_species(s);
                 npb = 0;
@@ -1428,12 +1427,12 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
         const int ovf0 = S.slots - S.ovf_cap;           // first slot of the overflow region
         auto fetch = [&](int q) { fetch_particle(P, src, q); };
         if (n > 0 && s != s0) fetch(tid);                // the first species: loaded during the set-up
-        for (int pb = 0; pb < n; pb += kBlock) {
+        for (int pb = 0; pb < n; pb += NT) {
             const int p = pb + tid;
             const bool valid = p < n;
             const int code = nx_code, id = nx_id;
             R d[3] = {nx_d[0], nx_d[1], nx_d[2]}, u[3] = {nx_u[0], nx_u[1], nx_u[2]};
-            if (pb + kBlock < n) fetch(p + kBlock);
+            if (pb + NT < n) fetch(p + NT);
             const int lx = code & ((1 << tsx) - 1), ly = (code >> tsx) & ((1 << (tsxy - tsx)) - 1), lz = code >> tsxy;
             const int ix = g.o[0] + lx, iy = g.o[1] + ly, iz = g.o[2] + lz;
             // a particle of the tile's ranges has its cell in the tile; a code
@@ -1653,7 +1652,7 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
     auto load_leavers = [&](int q0) {
 #pragma unroll
         for (int h = 0; h < kHand; ++h) {
-            const int q = q0 + h * kBlock;
+            const int q = q0 + h * NT;
             hsp[h] = -1;
             if (q < ntot) {
                 int s = 0;
@@ -1680,7 +1679,7 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
 
     // 6. flush the tile current to HBM (integer sums: order-independent)
     const int mJX = 65536 / g.JX + 1, mJY = 65536 / g.JY + 1;
-    for (int q = tid; q < g.JN; q += kBlock) {
+    for (int q = tid; q < g.JN; q += NT) {
         const JT v0 = jl[q], v1 = jl[g.JN + q], v2 = jl[2 * g.JN + q];
         if (v0 != JT(0) || v1 != JT(0) || v2 != JT(0)) {
             const int jk = div_small(q, mJX), i = q - jk * JX;
@@ -1704,8 +1703,8 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
     }
     __syncthreads();
     // 7c. store each loaded leaver at its claimed slot, then load the next
-    //     batch (tiles with more than kHand * kBlock leavers)
-    for (int q0 = tid; q0 < ntot; q0 += kHand * kBlock) {
+    //     batch (tiles with more than kHand * NT leavers)
+    for (int q0 = tid; q0 < ntot; q0 += kHand * NT) {
         if (q0 != tid) load_leavers(q0);
 #pragma unroll
         for (int h = 0; h < kHand; ++h) {
@@ -1746,6 +1745,30 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
             if (at >= 0) write_particle<FIX != 0>(sh_q[s], at, wide, hcell[h], code, hd[h], hu[h], hid[h]);
         }
     }
+}
+
+// FP32 form: four waves per SIMD (at most 128 VGPRs), the occupancy that
+// hides the latency of the LDS gather and of the particle loads best on
+// gfx950.  FP64 form: three (at most 168 VGPRs; with its 64-entry queues a
+// 4x4x4 block's LDS allows three blocks per CU as well).
+template <typename R, int FIX, int WALLS, int F4>
+__global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const BoxDev<R> *__restrict__ boxes,
+                                                                           const Item *__restrict__ items, StepConst<R> C)
+{
+    push_block<R, FIX, WALLS, F4, kBlock>(boxes, items, C);
+}
+
+// Launches that leave CUs idle take more threads per tile (wide_threads): the
+// time of such a launch is one tile's chain of set-up, iterations and hand-over,
+// and a wave then makes fewer iterations.  Step time with 256 / 512 / 1024
+// threads: 16^3 cells at 8 pairs per cell 23.0 / 20.5 / 19.2 us, at 256 221 / 156 /
+// 146; 24^3 at 64 (216 tiles) 70.1 / 52.9 / 50.2; 32^3 at 64 (512 tiles) 87.8 / 82.2 / -;
+// FP64 24^3 at 16 40.2 / 35.8 / 37.4.
+template <typename R, int F4, int NT>
+__global__ void __launch_bounds__(NT) wide_push_kernel(const BoxDev<R> *__restrict__ boxes,
+                                                       const Item *__restrict__ items, StepConst<R> C)
+{
+    push_block<R, 1, 0, F4, NT>(boxes, items, C);
 }
 
 // ------------------------------------------------------------- Yee updates
@@ -2179,7 +2202,7 @@ __global__ void __launch_bounds__(kBlock) half_step_kernel(const BoxDev<R> *__re
     R *coef = reinterpret_cast<R *>(smem);
     R *re = reinterpret_cast<R *>(smem + lds.coef);
     R *node = reinterpret_cast<R *>(smem + lds.coef + lds.stage);
-    tile_coefs<R, 0, 0, F4, false>(B, g, TileGrid<R>(B, g), C.dt, coef, re, re + 3 * g.JN, node, []() { return true; });
+    tile_coefs<R, 0, 0, F4, false, kBlock>(B, g, TileGrid<R>(B, g), C.dt, coef, re, re + 3 * g.JN, node, []() { return true; });
     for (int s = 0; s < C.nsp; ++s) {
         if (!((mask >> s) & 1u)) continue;
         const SpeciesDev<R> &S = B.sp[s];
@@ -2463,24 +2486,30 @@ __global__ void __launch_bounds__(64) diag_collect_kernel(const BoxDev<R> *__res
 
 template <typename R>
 size_t push_lds_bytes(int t0, int t1, int t2) { return tile_lds<R>(t0, t1, t2).total(); }
+template <typename R>
+size_t wide_lds_bytes(int threads) { return tile_lds<R>(4, 4, 4, threads / 64).total(); }
 
 template <typename R>
 hipError_t launch_push(const BoxDev<R> *boxes, const Item *items, int nitems, size_t lds, const StepConst<R> &C,
-                       int fixed444, int walls, int faraday4, hipStream_t st)
+                       int fixed444, int walls, int faraday4, int wide, hipStream_t st)
 {
     // dynamic LDS beyond 64 KiB has to be allowed per kernel: the limit each
     // variant was last raised to, raised again when a launch needs more
-    static size_t raised[6] = {65536, 65536, 65536, 65536, 65536, 65536};
-    auto go = [&](auto kern, int v) -> hipError_t {
+    static size_t raised[10] = {65536, 65536, 65536, 65536, 65536, 65536, 65536, 65536, 65536, 65536};
+    auto go = [&](auto kern, int v, int threads = kBlock) -> hipError_t {
         if (lds > raised[v]) {
             const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
             raised[v] = lds;
         }
-        hipLaunchKernelGGL(kern, dim3(nitems), dim3(kBlock), lds, st, boxes, items, C);
+        hipLaunchKernelGGL(kern, dim3(nitems), dim3(threads), lds, st, boxes, items, C);
         return hipGetLastError();
     };
+    if constexpr (sizeof(R) == 4) {
+        if (wide == 1024) return faraday4 ? go(wide_push_kernel<R, 1, 1024>, 9, 1024) : go(wide_push_kernel<R, 0, 1024>, 8, 1024);
+    }
+    if (wide) return faraday4 ? go(wide_push_kernel<R, 1, 512>, 7, 512) : go(wide_push_kernel<R, 0, 512>, 6, 512);
     // walls and the fourth-order solver are never combined (pic_plan refuses it)
     if (walls) return fixed444 ? go(push_kernel<R, 1, 1, 0>, 3) : go(push_kernel<R, 0, 1, 0>, 2);
     if (faraday4) return fixed444 ? go(push_kernel<R, 1, 0, 1>, 5) : go(push_kernel<R, 0, 0, 1>, 4);
@@ -2784,7 +2813,8 @@ hipError_t launch_spectrum(const BoxDev<R> *boxes, int box, const int n[3], int 
 #define PIC_INSTANTIATE(R)                                                                                     \
     template size_t push_lds_bytes<R>(int, int, int);                                                         \
     template hipError_t launch_push<R>(const BoxDev<R> *, const Item *, int, size_t, const StepConst<R> &,   \
-                                       int, int, int, hipStream_t);                                           \
+                                       int, int, int, int, hipStream_t);                                      \
+    template size_t wide_lds_bytes<R>(int);                                                                    \
     template hipError_t launch_fields<R>(const BoxDev<R> *, const CellBlock *, int, R, int, int, int, int,     \
                                          Watch, hipStream_t);                                                        \
     template hipError_t launch_advance_b<R>(const BoxDev<R> *, const CellBlock *, int, R, hipStream_t);       \

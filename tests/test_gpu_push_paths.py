@@ -67,3 +67,32 @@ def test_particles_enter_empty_tiles(fp64, kw):
         assert np.abs(G.wrap_delta(x, st.x[st.species == sp], dims)).max() < 10 * tol
         assert G.u_rel_err(u, st.u[st.species == sp], 1e-2).max() < 10 * tol
     s.close()
+
+
+@pytest.mark.parametrize("fp64", [False, True])
+@pytest.mark.parametrize("dims", [(24, 24, 28), (32, 24, 32), (32, 36, 29)], ids=["252_tiles", "384_tiles", "576_tiles"])
+def test_block_sizes(dims, fp64):
+    # one tile per CU, two, and more: the push with 1024 (FP32), 512 and 256
+    # threads per tile against the oracle, at a density that gives a wave none to
+    # several particles of a tile
+    rng = np.random.default_rng(dims[2])
+    n = 12000
+    s = G.sim(dims, 10.0, 16.0, [n, n], fp64=fp64)
+    st = G.oracle_state(dims, 10.0, 16.0)
+    e, b = G.random_fields(rng, int(np.prod(dims)), 0.02, 0.2)
+    side = np.array(dims) / np.array([1.0, 6.0, 1.0])        # a dense slab, the rest empty
+    parts = [(rng.uniform(0, 1, (n, 3)) * side, 0.7 * rng.standard_normal((n, 3))) for _ in range(2)]
+    G.start(s, st, parts, e=e, b=b, fp64=fp64)
+    s.step(4)
+    st.step(4)
+    tol = 1e-11 if fp64 else 2e-5
+    for sp in range(2):
+        x, u, ids = s.particles(0, sp)
+        assert np.array_equal(ids, np.arange(n))
+        assert G.u_rel_err(u, st.u[st.species == sp], 1e-2).max() < tol
+        assert np.abs(G.wrap_delta(x, st.x[st.species == sp], dims)).max() < 10 * tol
+    e1, b1, _ = s.fields(0)
+    assert np.abs(e1 - st.e).max() < tol * np.abs(st.e).max()
+    assert np.abs(b1 - st.b).max() < tol * np.abs(st.b).max()
+    assert s.diag(0)["flags"] == 0
+    s.close()
