@@ -377,13 +377,17 @@ __host__ __device__ inline size_t queue_bytes(int waves)
 // coefficients of every cell (48 values), the piece queues, then a region that
 // first holds the staged raw fields and node fields and then the tile current.
 // Values per cell in the gather's coefficient table: 8 per field component,
-// padded from 48 to 52 so that the 16-byte reads of lanes in different cells
-// start on different LDS banks.  (A coefficient-major table, one dword per
-// lane per read, ran the push 43 % slower.)
-constexpr int kCoef = 52;
+// and 16 bytes more, so that a record is an odd number of 16-byte units and the
+// 16-byte reads of lanes in different cells start on different LDS banks: 52
+// values in FP32, 50 in FP64, whose push the LDS bounds (busy for 0.81 of it;
+// with 52 values there too, half the banks served all reads: 0.958 against 0.932 ms, 33.5 M particles).  (A
+// coefficient-major table, one dword per lane per read, ran the push 43 %
+// slower.)
+template <typename R>
+constexpr int kCoef = 48 + 16 / (int)sizeof(R);
 
 // LDS of one push block for tiles of t0 x t1 x t2 cells, three regions:
-//   [coef]   the gather's coefficient table (kCoef values per cell);
+//   [coef]   the gather's coefficient table (kCoef<R> values per cell);
 //   [stage]  the piece queues during the particle loop, the staged raw e and
 //            b (tile plus halo) during set-up;
 //   [union]  the node fields during set-up, the tile current afterwards.
@@ -402,7 +406,7 @@ __host__ __device__ inline TileLds tile_lds(int t0, int t1, int t2, int waves = 
     const size_t raw = 3 * (jn + bn) * sizeof(R), q = queue_bytes<R>(waves);
     const size_t nodes = 6 * nn * sizeof(R), jb = 3 * jn * sizeof(typename JType<R>::T);
     TileLds L;
-    L.coef = (nc * kCoef * sizeof(R) + 15) & ~size_t(15);
+    L.coef = (nc * kCoef<R> * sizeof(R) + 15) & ~size_t(15);
     L.stage = ((raw > q ? raw : q) + 15) & ~size_t(15);
     L.uni = ((nodes > jb ? nodes : jb) + 15) & ~size_t(15);
     return L;
@@ -985,7 +989,7 @@ __device__ __forceinline__ bool tile_coefs(const BoxDev<R> &B, const TileGeom<R>
         for (int q = tid; q < ncell; q += NT) {
             const int jk = div_small(q, mEX), i = q - jk * g.ext[0];
             const int k = div_small(jk, mEY), j = jk - k * g.ext[1];
-            R *cf = coef + kCoef * (i | (j << tsx) | (k << tsxy));
+            R *cf = coef + kCoef<R> * (i | (j << tsx) | (k << tsxy));
             const int m = i + NX * j + NXY * k;
 #pragma unroll
             for (int c = 0; c < 6; ++c) {
@@ -1315,7 +1319,7 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
 
             // gather, Boris step, move
             const uint32_t pc = __umul24(code, 0x1041u) & kThrees;
-            const R *cf = coef + __umul24(kCoef, code);
+            const R *cf = coef + __umul24(kCoef<R>, code);
             R E[3], Bf[3], D[3];
 #pragma unroll
             for (int c = 0; c < 3; ++c) E[c] = trilinear_eval(cf + 8 * c, d);
@@ -1445,7 +1449,7 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
             if (!inside) {
                 gather_global<R, F4>(B, ix, iy, iz, d, hdt, E, Bf);
             } else {
-                const R *cf = coef + __umul24(kCoef, lx | (ly << tsx) | (lz << tsxy));
+                const R *cf = coef + __umul24(kCoef<R>, lx | (ly << tsx) | (lz << tsxy));
                 R F[6];
 #pragma unroll
                 for (int c = 0; c < 6; ++c) F[c] = trilinear_eval(cf + 8 * c, d);
@@ -2211,7 +2215,7 @@ __global__ void __launch_bounds__(kBlock) half_step_kernel(const BoxDev<R> *__re
             const PSlot<R> ps = slot_at(S.buf[dst], start + p);
             const R d[3] = {ps.d(0), ps.d(1), ps.d(2)};
             R u[3] = {ps.u(0), ps.u(1), ps.u(2)}, E[3], Bf[3];
-            const R *cf = coef + kCoef * (int)ps.code();
+            const R *cf = coef + kCoef<R> * (int)ps.code();
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 E[c] = trilinear_eval(cf + 8 * c, d);
