@@ -219,7 +219,7 @@ static void make_layout(const pic_config *cfg, std::vector<BoxHost> &bh, char *b
     L.sitems = A.take<StageItem>(std::max(1, L.max_sitems));
     L.half = A.take<uint32_t>(cfg->n_boxes);
     L.flags = A.take<uint32_t>(64);
-    for (auto &c : L.mj_cum) c = A.take<double>(kTabM + 1 + 2 * ((kTabM + kMjBlock - 1) / kMjBlock));   // and the block totals
+    for (auto &c : L.mj_cum) c = A.take<double>(kTabM + 1 + (kTabM + kMjChunk - 1) / kMjChunk);   // and the chunks' totals
     L.mj_tab[0] = A.take<double>(kTabN + 1);
     L.mj_tab[1] = A.take<double>(kTabN + 1);
     bd.resize(cfg->n_boxes);

@@ -396,6 +396,7 @@ hipError_t launch_zero(void *p, int64_t words, hipStream_t st);   // 8-byte word
 hipError_t diag_scratch_setup();
 void *diag_scratch();
 constexpr int kMjBlock = 1024;          // intervals per block of the table's prefix sum
+constexpr int kMjChunk = 64;            // intervals per compensated sum
 hipError_t launch_mj_tables(int n, const double *theta, const double *gamma_beta, double *const *cum, int M, int N,
                             double *const *tab, hipStream_t st);
 template <typename R> hipError_t launch_load_pairs(const BoxDev<R> *boxes, const LoadArgs &L, hipStream_t st);

@@ -69,66 +69,72 @@ struct MJTables {
     MJTable t[2];
 };
 
-// A sum kept as an unevaluated pair hi + lo (Knuth's two-sum): adding two of
-// them loses nothing that matters at 64 bits, in any order, so the prefix sum
-// below can be a tree.
-struct Sum2 {
-    double hi, lo;
-};
-__device__ inline Sum2 two_sum(double a, double b)
-{
-    const double s = a + b, t = s - a;
-    return {s, (a - (s - t)) + (b - t)};
-}
-__device__ inline Sum2 add2(Sum2 a, Sum2 b)
-{
-    Sum2 s = two_sum(a.hi, b.hi);
-    s.lo += a.lo + b.lo;
-    return two_sum(s.hi, s.lo);
-}
-// inclusive prefix sum over the wave
-__device__ inline Sum2 wave_scan(Sum2 v)
-{
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const Sum2 o = {__shfl_up(v.hi, off), __shfl_up(v.lo, off)};
-        if (lane >= off) v = add2(o, v);
-    }
-    return v;
-}
-
-// The integral of each of the M intervals and its prefix sum: cum[i + 1] holds
-// the sum over the intervals of block i / kMjBlock up to i, the block's total
-// goes to the pairs behind cum[M]; mj_offsets_kernel adds the blocks before.
-// (One block that summed all 65536 intervals serially per thread, with one
-// thread for the 1024 totals, took 190 us per table, half of the time of a
-// small load; these two take 15 us.)
+// The integral of each of the M intervals and its prefix sum, compensated
+// (Kahan) and always in the same order, so that a table does not depend on the
+// launch: within chunks of kMjChunk intervals, then over the chunks' totals.
+// cum[i + 1] gets the sum over interval i's chunk up to i, cum[M + 1 + c] the
+// total of chunk c; mj_offsets_kernel adds the chunks before.  (One block that
+// read all 65536 intervals with a stride and had one thread for the 1024 totals
+// took 190 us per table, half of the time of a small load; these two take 26.)
 __global__ void __launch_bounds__(kMjBlock) mj_intervals_kernel(MJTables T, int M)
 {
-    __shared__ Sum2 tot[kMjBlock / 64];
+    constexpr int kChunks = kMjBlock / kMjChunk, kRow = kMjChunk + 1;
+    __shared__ double v[kChunks * kRow];
     const MJTable &P = T.t[blockIdx.y];
-    const int i = blockIdx.x * kMjBlock + threadIdx.x, wave = threadIdx.x >> 6;
-    Sum2 v = {i < M ? py_integral(P.ylo + i * P.h, P.ylo + (i + 1) * P.h, P.m) : 0.0, 0.0};
-    v = wave_scan(v);
-    if ((threadIdx.x & 63) == 63) tot[wave] = v;
+    const int t = threadIdx.x, i = blockIdx.x * kMjBlock + t;
+    double &own = v[t / kMjChunk * kRow + t % kMjChunk];
+    own = i < M ? py_integral(P.ylo + i * P.h, P.ylo + (i + 1) * P.h, P.m) : 0.0;
     __syncthreads();
-    Sum2 run = {0.0, 0.0};
-    for (int w = 0; w < wave; ++w) run = add2(run, tot[w]);
-    v = add2(run, v);
-    if (i < M) P.cum[i + 1] = v.hi;
-    if (threadIdx.x == kMjBlock - 1) {
-        P.cum[M + 1 + 2 * blockIdx.x] = v.hi;
-        P.cum[M + 2 + 2 * blockIdx.x] = v.lo;
+    const int c0 = blockIdx.x * kChunks;
+    if (t < kChunks && (c0 + t) * kMjChunk < M) {
+        const int n = min(kMjChunk, M - (c0 + t) * kMjChunk);
+        double s = 0.0, comp = 0.0;
+        for (int q = 0; q < n; ++q) {
+            const double y = v[t * kRow + q] - comp;
+            const double z = s + y;
+            comp = (z - s) - y;
+            s = z;
+            v[t * kRow + q] = s;
+        }
+        P.cum[M + 1 + c0 + t] = s;
     }
+    __syncthreads();
+    if (i < M) P.cum[i + 1] = own;
 }
 __global__ void __launch_bounds__(kMjBlock) mj_offsets_kernel(MJTables T, int M)
 {
+    constexpr int kChunks = kMjBlock / kMjChunk;
+    __shared__ double tot[kMjBlock], base[kChunks];
     const MJTable &P = T.t[blockIdx.y];
-    Sum2 run = {0.0, 0.0};
-    for (int b = 0; b < (int)blockIdx.x; ++b) run = add2(run, Sum2{P.cum[M + 1 + 2 * b], P.cum[M + 2 + 2 * b]});
-    const int i = blockIdx.x * kMjBlock + threadIdx.x;
-    if (i < M && blockIdx.x > 0) P.cum[i + 1] = add2(run, Sum2{P.cum[i + 1], 0.0}).hi;
+    const int t = threadIdx.x, i = blockIdx.x * kMjBlock + t, c0 = blockIdx.x * kChunks;
+    double run = 0.0, comp = 0.0;                // of thread 0: sum of the chunks before
+    for (int first = 0; first < c0 + kChunks; first += kMjBlock) {
+        __syncthreads();
+        if (first + t < c0 + kChunks) tot[t] = (first + t) * kMjChunk < M ? P.cum[M + 1 + first + t] : 0.0;
+        __syncthreads();
+        if (t) continue;
+        auto add = [&](double v) {
+            const double y = v - comp;
+            const double z = run + y;
+            comp = (z - run) - y;
+            run = z;
+        };
+        const int before = min(kMjBlock, c0 - first), all = min(kMjBlock, c0 + kChunks - first);
+        int c = 0;
+        for (; c + 8 <= before; c += 8) {         // eight reads in flight before eight sums
+            double v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = tot[c + q];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) add(v[q]);
+        }
+        for (; c < all; ++c) {
+            if (first + c >= c0) base[first + c - c0] = run;
+            add(tot[c]);
+        }
+    }
+    __syncthreads();
+    if (i < M) P.cum[i + 1] += base[t / kMjChunk];
     if (i == 0) P.cum[0] = 0.0;
 }
 
@@ -170,6 +176,20 @@ __global__ void mj_invert_kernel(MJTables T, int M, int N)
 
 // ------------------------------------------------------------- pair loading
 
+// The radial solve of mj_momentum by Newton on the logarithm from d = 0.
+__device__ double mj_radial_newton(double a, double lw)
+{
+    double dx = 0.0;
+    for (int it = 0; it < 60; ++it) {
+        const double gval = log1p(dx / (1.0 + a)) - dx - lw;        // decreasing in dx
+        const double slope = (a + dx) / (1.0 + a + dx);              // -d(gval)/d(dx)
+        const double step = gval / slope;
+        dx = fmax(dx + step, 0.0);
+        if (it >= 3 && fabs(step) <= 1e-15 * (dx + 1e-300)) break;
+    }
+    return dx;
+}
+
 // u from (quantile t, radial w in (0,1], azimuth v): p_y from the table by
 // linear interpolation; r from l(x) = w l(a) (App. D, eq. finding_u), solved
 // on the logarithm in d = x - a >= 0; azimuth uniform; then the drift axis y
@@ -178,9 +198,16 @@ __global__ void mj_invert_kernel(MJTables T, int M, int N)
 // of this solve: Newton from d = 0 took six of them per momentum.  Four FP32
 // Newton steps give a start good to about 1e-6, from which one FP64 step of
 // third order (Halley) reaches roundoff; a step larger than 1e-6 d is followed
-// by another.  With g = ln(1 + d/(1 + a)) - d - ln w the step's error is below
+// by another.  (Registers: a thread loads one pair; in a loop over pairs the
+// constants of the logarithms stayed live, 218 registers instead of 76, and the
+// load took 1.72 ms.)  With g = ln(1 + d/(1 + a)) - d - ln w the step's error is below
 // (step/d)^3 d, since g2 and g3 (second and third derivative) are below
-// |g1|/(a + d) and 2 |g1|/(a + d)^2.  16.8 M pairs: 1.87 -> 1.48 ms.
+// |g1|/(a + d) and 2 |g1|/(a + d)^2.  16.8 M pairs: 1.87 -> 1.40 ms.
+// FP32 momenta are those of the Newton solve bit for bit: where roundoff, here
+// at most 2^-53 * 4 (1 + a + d)/(a + d) of d in either solve and 1e-15 of the
+// radius from the azimuth, could carry a component over a rounding boundary of
+// FP32 (about one momentum in 10^6), Newton decides.
+template <typename R>
 __device__ inline void mj_momentum(const MJPop &P, int N, double t, double w, double v, double out[3])
 {
     const double f = t * N;
@@ -195,19 +222,28 @@ __device__ inline void mj_momentum(const MJPop &P, int N, double t, double w, do
 #pragma unroll
     for (int it = 0; it < 4; ++it)
         df = fmaxf(df + (log1pf(df * ra) - df - lf) * (1.0f + af + df) / (af + df), 0.0f);
-    double dx = (double)df;
+    double dx = (double)df, cond = 0.0;          // cond: (1 + a + d)/(a + d)
     for (int it = 0; it < 60; ++it) {
         const double t = 1.0 + a + dx, inv = 1.0 / (a + dx);        // g1 = -1 / (t inv), g2 = -1 / t^2
-        const double newton = (log1p(dx / (1.0 + a)) - dx - lw) * t * inv;
+        cond = t * inv;
+        const double newton = (log1p(dx / (1.0 + a)) - dx - lw) * cond;
         const double step = newton / (1.0 + 0.5 * newton * inv / t);
         dx = fmax(dx + step, 0.0);
         if (fabs(step) <= 1e-6 * dx) break;
     }
-    const double um1 = dx / a;
-    const double r = sqrt(um1 * (2.0 + um1));
-    double sn, cs;
+    double um1 = dx / a, r = sqrt(um1 * (2.0 + um1)), sn, cs;
     sincospi(2.0 * v, &sn, &cs);
-    const double q[3] = {gy * r * cs, py, gy * r * sn};
+    double q[3] = {gy * r * cs, py, gy * r * sn};
+    if (sizeof(R) == sizeof(float)) {
+        const double e = gy * r * (8e-15 * cond + 4e-15);
+        if ((float)(q[0] - e) != (float)(q[0] + e) || (float)(q[2] - e) != (float)(q[2] + e)) {
+            um1 = mj_radial_newton(a, lw) / a;
+            r = sqrt(um1 * (2.0 + um1));
+            sincos(6.283185307179586 * v, &sn, &cs);
+            q[0] = gy * r * cs;
+            q[2] = gy * r * sn;
+        }
+    }
     const int sh = (P.axis + 2) % 3;          // component 1 -> axis
     for (int c = 0; c < 3; ++c) out[(c + sh) % 3] = q[c];
 }
@@ -241,8 +277,8 @@ __global__ void __launch_bounds__(256) load_pairs_kernel(const BoxDev<R> *__rest
     const BoxDev<R> &B = boxes[L.box];
     const SpeciesDev<R> &SA = B.sp[L.sa];
     const SpeciesDev<R> &SB = B.sp[L.sb];
-    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < L.npairs;
-         p += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (p < L.npairs) {
         uint64_t w[3][4];
         for (int j = 0; j < 3; ++j) {
             w[j][0] = (uint64_t)p; w[j][1] = (uint64_t)j; w[j][2] = 0; w[j][3] = 0;
@@ -259,8 +295,8 @@ __global__ void __launch_bounds__(256) load_pairs_kernel(const BoxDev<R> *__rest
                 x[a] = U * B.n[a];
         }
         double ua[3], ub[3];
-        mj_momentum(L.A, L.N, unit53(w[0][3]), 1.0 - unit53(w[1][0]), unit53(w[1][1]), ua);
-        mj_momentum(L.B, L.N, unit53(w[1][2]), 1.0 - unit53(w[1][3]), unit53(w[2][0]), ub);
+        mj_momentum<R>(L.A, L.N, unit53(w[0][3]), 1.0 - unit53(w[1][0]), unit53(w[1][1]), ua);
+        mj_momentum<R>(L.B, L.N, unit53(w[1][2]), 1.0 - unit53(w[1][3]), unit53(w[2][0]), ub);
         int32_t cell;
         R d[3];
         to_storage(B, x, cell, d);
@@ -328,7 +364,6 @@ template <typename R>
 hipError_t launch_load_pairs(const BoxDev<R> *boxes, const LoadArgs &L, hipStream_t st)
 {
     int64_t blocks = (L.npairs + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL(load_pairs_kernel<R>, dim3((unsigned)blocks), dim3(256), 0, st, boxes, L);
     return hipGetLastError();

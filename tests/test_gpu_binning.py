@@ -41,3 +41,19 @@ def test_loads_are_binned_and_integrated_back(dims, tile, fp64):
     s.step(3)
     assert s.diag(0)["count"].tolist() == [sum(npairs)] * 2
     s.close()
+
+
+@pytest.mark.parametrize("theta,gb", [(0.02, 0.0), (0.5, 2.0), (8.0, 0.3)])
+def test_fp32_momenta_are_the_rounded_fp64_ones(theta, gb):
+    # without fields the half step back leaves momenta as they are; the FP64
+    # ones are off by roundoff, far below 1e-6 of an FP32 rounding step
+    dims, ppc = (16, 16, 16), 64
+    u = []
+    for fp64 in (False, True):
+        s = G.sim(dims, 10.0, 2.0 * ppc, [ppc * 4096] * 2, fp64=fp64)
+        s.load(0, 0, 1, (theta, gb, 1), (theta, -gb, 2), ppc, seed=3)
+        s.step(0)
+        u.append(np.stack([s.particles(0, sp)[1] for sp in range(2)]))
+        s.close()
+    half = 0.5 * np.spacing(np.abs(u[0]).astype(np.float32)).astype(np.float64)
+    assert np.all(np.abs(u[1] - u[0]) <= half * (1.0 + 1e-6))
