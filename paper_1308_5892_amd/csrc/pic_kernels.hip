@@ -370,7 +370,7 @@ constexpr int kWaves = kBlock / 64;
 template <typename R>
 __host__ __device__ inline size_t queue_bytes(int waves)
 {
-    return (size_t)waves * QCap<R>::value * (2 * sizeof(int32_t) + 6 * sizeof(R));
+    return (size_t)waves * QCap<R>::value * (sizeof(int32_t) + 6 * sizeof(R));
 }
 
 // Bytes of dynamic LDS for a tile with edges (t0, t1, t2): the trilinear
@@ -385,6 +385,24 @@ __host__ __device__ inline size_t queue_bytes(int waves)
 // slower.)
 template <typename R>
 constexpr int kCoef = 48 + 16 / (int)sizeof(R);
+
+// Strides of the tile current in LDS, (t + 3)^3 points per component.  4x4x4
+// tiles: rows of 7 and planes of 52, with which the points of the 64 cells, at
+// equal moves, lie more evenly over the 32 banks of 8 bytes that the adds use than
+// with planes of 49 (sum over the banks of the square of their load 152 against
+// 160, 16 cells of an x-z plane 16 against 24).  Push with planes of 52
+// against 49: 33.5 M thermal particles 500 against 510 us, in FP64 895 against
+// 916, two beams 570 against 603, Harris sheet 409 against 420.  Planes of 60 are
+// as fast and take more room; rows of 8 with planes of 60 were slower for beams
+// (694 us: the rows of a plane then share banks).
+struct CurrentGrid {
+    int x, xy, n;
+    __host__ __device__ constexpr CurrentGrid(int t0, int t1, int t2)
+        : x(t0 == 4 && t1 == 4 && t2 == 4 ? 7 : t0 + 3), xy(t0 == 4 && t1 == 4 && t2 == 4 ? 52 : (t0 + 3) * (t1 + 3)),
+          n(xy * (t2 + 3))
+    {
+    }
+};
 
 // LDS of one push block for tiles of t0 x t1 x t2 cells, three regions:
 //   [coef]   the gather's coefficient table (kCoef<R> values per cell);
@@ -404,7 +422,8 @@ __host__ __device__ inline TileLds tile_lds(int t0, int t1, int t2, int waves = 
     const size_t jn = (size_t)(t0 + 3) * (t1 + 3) * (t2 + 3);
     const size_t bn = (size_t)(t0 + 2) * (t1 + 2) * (t2 + 2);
     const size_t raw = 3 * (jn + bn) * sizeof(R), q = queue_bytes<R>(waves);
-    const size_t nodes = 6 * nn * sizeof(R), jb = 3 * jn * sizeof(typename JType<R>::T);
+    const size_t nodes = 6 * nn * sizeof(R);
+    const size_t jb = 3 * (size_t)CurrentGrid(t0, t1, t2).n * sizeof(typename JType<R>::T);
     TileLds L;
     L.coef = (nc * kCoef<R> * sizeof(R) + 15) & ~size_t(15);
     L.stage = ((raw > q ? raw : q) + 15) & ~size_t(15);
@@ -541,9 +560,10 @@ __device__ inline void first_breakpoint(const R d[3], const R D[3], const int di
 }
 
 // Meta word of a queued move: per axis a the crossing direction + 1 (bits 8a,
-// 8a + 1), next piece k (bits 2-3), crossings nb (4-5) and the crossing axes
-// in order o0, o1, o2 (10-15).
-constexpr int kMetaK = 2, kMetaNb = 4, kMetaO = 10;
+// 8a + 1), next piece k (bits 2-3), crossings nb (4-5), the crossing axes in
+// order o0, o1, o2 (10-15), the tile current's index of the home cell (18-30; at
+// most 1064, in 8x8x8 tiles) and the sign of the species (31).
+constexpr int kMetaK = 2, kMetaNb = 4, kMetaO = 10, kMetaJ = 18;
 __device__ inline int move_meta(int k, int nb, int o0, int o1, int o2, const int dir[3])
 {
     return (k << kMetaK) | (nb << kMetaNb) | (o0 << kMetaO) | (o1 << (kMetaO + 2)) | (o2 << (kMetaO + 4)) |
@@ -1154,7 +1174,9 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
     }
 
     const TileGrid<R> grid(B, g);
-    const int JX = g.JX, JXY = g.JX * g.JY;
+    // strides of the tile current
+    const CurrentGrid cg = FIX ? CurrentGrid(4, 4, 4) : CurrentGrid(1 << B.tshift[0], 1 << B.tshift[1], 1 << B.tshift[2]);
+    const int JX = cg.x, JXY = cg.xy;
     const R hdt = R(0.5) * C.dt;
 
     // the particle loops load each lane's next particle one iteration ahead
@@ -1196,7 +1218,7 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
     // the other copy is zero already): two thirds of the tiles of a 796 x 632 x 4
     // Harris sheet, whose push takes 0.515 ms with this and 0.548 without
     if (!any) return;
-    for (int q = tid; q < 3 * g.JN; q += NT) jl[q] = JT(0);
+    for (int q = tid; q < 3 * cg.n; q += NT) jl[q] = JT(0);
     __syncthreads();
 
     // 5. particles of every species: gather, push, move, deposit, re-bin
@@ -1207,26 +1229,23 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             const int b1 = a == 2 ? 0 : a + 1, b2 = a == 0 ? 2 : a - 1;
-            joff[a][0] = a * g.JN;
-            joff[a][1] = a * g.JN + S[b2];
-            joff[a][2] = a * g.JN + S[b1];
-            joff[a][3] = a * g.JN + S[b1] + S[b2];
+            joff[a][0] = a * cg.n;
+            joff[a][1] = a * cg.n + S[b2];
+            joff[a][2] = a * cg.n + S[b1];
+            joff[a][3] = a * cg.n + S[b1] + S[b2];
         }
     }
-    // this wave's queue of unfinished moves: home-cell index (sign bit =
-    // species sign), meta word (move_meta), start of the next piece and end
-    // of the move
+    // this wave's queue of unfinished moves: meta word (move_meta), start of
+    // the next piece and end of the move
     const int wave = tid >> 6, lane = __lane_id();
     constexpr int kQCap = QCap<R>::value;
-    int32_t *qidx = reinterpret_cast<int32_t *>(qmem) + wave * kQCap;
-    int32_t *qmeta = reinterpret_cast<int32_t *>(qmem) + (kWaves + wave) * kQCap;
-    R *qval = reinterpret_cast<R *>(qmem + 2 * kWaves * kQCap * sizeof(int32_t)) + wave * 6 * kQCap;
+    int32_t *qmeta = reinterpret_cast<int32_t *>(qmem) + wave * kQCap;
+    R *qval = reinterpret_cast<R *>(qmem + kWaves * kQCap * sizeof(int32_t)) + wave * 6 * kQCap;
     int qhead = 0, qcount = 0;                    // wave-uniform
-    auto put = [&](bool has, int32_t w, int32_t meta, const R ps[3], const R x1[3]) {
+    auto put = [&](bool has, int32_t meta, const R ps[3], const R x1[3]) {
         const uint64_t mh = __ballot(has);
         if (has) {
             const int pos = (qhead + qcount + lane_rank(mh)) & (kQCap - 1);
-            qidx[pos] = w;
             qmeta[pos] = meta;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
@@ -1243,11 +1262,10 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         const int nq = min(qcount, 64);
-        int32_t w = 0, meta = 0;
+        int32_t meta = 0;
         R ps[3] = {R(0), R(0), R(0)}, x1[3] = {R(0), R(0), R(0)};
         if (lane < nq) {
             const int e = (qhead + lane) & (kQCap - 1);
-            w = qidx[e];
             meta = qmeta[e];
 #pragma unroll
             for (int a = 0; a < 3; ++a) { ps[a] = qval[a * kQCap + e]; x1[a] = qval[(3 + a) * kQCap + e]; }
@@ -1264,12 +1282,12 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
             int offc[3];
             R sv[3], dd[3];
             chain_piece(ps, x1, meta, k, pe, offc, sv, dd);
-            const int cb = (w & 0x7fffffff) + offc[0] + __mul24(JX, offc[1]) + __mul24(JXY, offc[2]);
-            const R sc = w < 0 ? -qscale_bits<R>() : qscale_bits<R>();
+            const int cb = ((meta >> kMetaJ) & 8191) + offc[0] + __mul24(JX, offc[1]) + __mul24(JXY, offc[2]);
+            const R sc = meta < 0 ? -qscale_bits<R>() : qscale_bits<R>();
             deposit_piece<R>(jl, cb, joff, sv, dd, sc);
             more = k < nb;
         }
-        put(more, w, meta + (1 << kMetaK), pe, x1);
+        put(more, meta + (1 << kMetaK), pe, x1);
     };
     // Particle loop of 4x4x4 tiles.  What bounds it: on the 64^3 thermal box
     // (33.5 M particles) the vector ALU, the LDS and HBM are each busy for
@@ -1292,6 +1310,7 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
         TileRanges src = ranges(s), nsrc = src;
         PBuf<R> P = B.sp[s].buf[C.cur], Q = B.sp[s].buf[C.cur ^ 1];
         R hk = R(0.5) * C.kq[s] * C.dt, scale = -C.qs[s] * qscale_bits<R>();
+        int32_t sgnbit = scale < R(0) ? (int32_t)0x80000000 : 0;
         int dst_start = __builtin_amdgcn_readfirstlane(sh_rng[s][4]), spare = B.sp[s].slots;
         const R dt = C.dt;
         // the first particles are waited for here: a wait at the loop's top
@@ -1355,7 +1374,7 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
             const bool c10 = lam[1] < lam[0], c20 = lam[2] < lam[0], c21 = lam[2] < lam[1];
             const bool f2 = c20 && c21;
             const R l0 = f2 ? lam[2] : (c10 ? lam[1] : lam[0]);
-            const int jb = (int)udot4(pc, 1u | (7u << 8) | (49u << 16)) + 57;
+            const int jb = (int)udot4(pc, 1u | ((uint32_t)cg.x << 8) | ((uint32_t)cg.xy << 16)) + 1 + cg.x + cg.xy;
             R p1[3] = {x1[0], x1[1], x1[2]};
             if (cross) {
                 const R q0 = clamp01(fma(l0, D[0], d[0])), q1 = clamp01(fma(l0, D[1], d[1])),
@@ -1394,8 +1413,8 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
                 const int nb = 3 - __popc(Fw & kOnes);
                 const int o012 = c10 ? (c20 ? (c21 ? 2 | (1 << 2) : 1 | (2 << 2)) | (0 << 4) : 1 | (2 << 4))
                                      : (c21 ? (c20 ? 2 | (1 << 4) : (2 << 2) | (1 << 4)) : (1 << 2) | (2 << 4));
-                put(valid && cross, scale < R(0) ? (int)((uint32_t)jb | 0x80000000u) : jb,
-                    (int)Fw | (1 << kMetaK) | (nb << kMetaNb) | (o012 << kMetaO), p1, x1);
+                put(valid && cross, (int)Fw | (1 << kMetaK) | (nb << kMetaNb) | (o012 << kMetaO) | (jb << kMetaJ) | sgnbit,
+                    p1, x1);
             }
             while (qcount >= 64) drain();
 
@@ -1406,6 +1425,7 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
                 Q = B.sp[s].buf[C.cur ^ 1];
                 hk = R(0.5) * C.kq[s] * C.dt;
                 scale = -C.qs[s] * qscale_bits<R>();
+                sgnbit = scale < R(0) ? (int32_t)0x80000000 : 0;
                 dst_start = __builtin_amdgcn_readfirstlane(sh_rng[s][4]);
                 spare = B.sp[s].slots;
             }
@@ -1578,7 +1598,7 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
                 const int cnt = (int)__popcll(__ballot(valid && inside && nb > 0));
                 while (qcount + cnt > kQCap) drain();
             }
-            put(valid && inside && nb > 0, jb | sgnbit, move_meta(1, nb, o0, o1, o2, dir), p1, x1);
+            put(valid && inside && nb > 0, move_meta(1, nb, o0, o1, o2, dir) | (jb << kMetaJ) | sgnbit, p1, x1);
             while (qcount >= 64) drain();
             if (WALLS && B.wall >= 0 && __ballot(hitw)) {
                 // the mirrored rest of the moves that hit a wall: a whole move
@@ -1598,7 +1618,7 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
                     const int cnt = (int)__popcll(__ballot(hitw && inside));
                     while (qcount + cnt > kQCap) drain();
                 }
-                put(hitw && inside, jb2 | sgnbit, move_meta(0, nb2, q0, q1, q2, db), P2, y1);
+                put(hitw && inside, move_meta(0, nb2, q0, q1, q2, db) | (jb2 << kMetaJ) | sgnbit, P2, y1);
                 if (hitw && !inside) {
                     PIC_GLOBAL JT *J = B.J;
                     deposit_rest(P2, D2, scale, [&](int a, int ox, int oy, int oz, JT q) {
@@ -1684,10 +1704,11 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
     // 6. flush the tile current to HBM (integer sums: order-independent)
     const int mJX = 65536 / g.JX + 1, mJY = 65536 / g.JY + 1;
     for (int q = tid; q < g.JN; q += NT) {
-        const JT v0 = jl[q], v1 = jl[g.JN + q], v2 = jl[2 * g.JN + q];
+        const int jk = div_small(q, mJX), i = q - jk * g.JX;
+        const int k = div_small(jk, mJY), j = jk - k * g.JY;
+        const JT *at = jl + i + JX * j + JXY * k;
+        const JT v0 = at[0], v1 = at[cg.n], v2 = at[2 * cg.n];
         if (v0 != JT(0) || v1 != JT(0) || v2 != JT(0)) {
-            const int jk = div_small(q, mJX), i = q - jk * JX;
-            const int k = div_small(jk, mJY), j = jk - k * g.JY;
             const int64_t gp = grid(i, j, k);
             if (v0 != JT(0)) atomic_add_global(&B.J[gp], v0);
             if (v1 != JT(0)) atomic_add_global(&B.J[B.nc + gp], v1);
