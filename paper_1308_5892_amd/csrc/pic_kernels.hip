@@ -373,16 +373,13 @@ __host__ __device__ inline size_t queue_bytes(int waves)
     return (size_t)waves * QCap<R>::value * (sizeof(int32_t) + 6 * sizeof(R));
 }
 
-// Bytes of dynamic LDS for a tile with edges (t0, t1, t2): the trilinear
-// coefficients of every cell (48 values), the piece queues, then a region that
-// first holds the staged raw fields and node fields and then the tile current.
 // Values per cell in the gather's coefficient table: 8 per field component,
 // and 16 bytes more, so that a record is an odd number of 16-byte units and the
 // 16-byte reads of lanes in different cells start on different LDS banks: 52
 // values in FP32, 50 in FP64, whose push the LDS bounds (busy for 0.81 of it;
-// with 52 values there too, half the banks served all reads: 0.958 against 0.932 ms, 33.5 M particles).  (A
-// coefficient-major table, one dword per lane per read, ran the push 43 %
-// slower.)
+// with 52 values there too, half the banks served all reads: 0.958 against
+// 0.932 ms, 33.5 M particles).  (A coefficient-major table, one dword per lane
+// per read, ran the push 43 % slower.)
 template <typename R>
 constexpr int kCoef = 48 + 16 / (int)sizeof(R);
 
@@ -1293,7 +1290,8 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
     // (33.5 M particles) the vector ALU, the LDS and HBM are each busy for
     // 0.67-0.75 of the launch, so it is written for few instructions and for
     // no wait that the data does not force (0.540 ms with the general loop,
-    // 0.510 ms with this one; 430 -> 376 VALU instructions per 64 particles):
+    // 0.510 ms with this one, 0.500 with CurrentGrid's planes; 430 -> 376 VALU
+    // instructions per 64 particles):
     // - cells, moves and bins are packed words (TileMove), every particle of
     //   the tile's ranges goes to the tile or to one next to it, and no lane
     //   takes a path of its own;

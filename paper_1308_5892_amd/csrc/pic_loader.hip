@@ -198,11 +198,11 @@ __device__ double mj_radial_newton(double a, double lw)
 // of this solve: Newton from d = 0 took six of them per momentum.  Four FP32
 // Newton steps give a start good to about 1e-6, from which one FP64 step of
 // third order (Halley) reaches roundoff; a step larger than 1e-6 d is followed
-// by another.  (Registers: a thread loads one pair; in a loop over pairs the
-// constants of the logarithms stayed live, 218 registers instead of 76, and the
-// load took 1.72 ms.)  With g = ln(1 + d/(1 + a)) - d - ln w the step's error is below
+// by another.  With g = ln(1 + d/(1 + a)) - d - ln w the step's error is below
 // (step/d)^3 d, since g2 and g3 (second and third derivative) are below
 // |g1|/(a + d) and 2 |g1|/(a + d)^2.  16.8 M pairs: 1.87 -> 1.40 ms.
+// (A thread loads one pair: in a loop over pairs the constants of the logarithms
+// stayed live, 218 registers instead of 76 and 1.72 ms.)
 // FP32 momenta are those of the Newton solve bit for bit: where roundoff, here
 // at most 2^-53 * 4 (1 + a + d)/(a + d) of d in either solve and 1e-15 of the
 // radius from the azimuth, could carry a component over a rounding boundary of
