@@ -1095,20 +1095,19 @@ int pic_set_particles(pic_ctx *ctx, int box, int species, const double *x, const
                      : set_particles_t<float>(ctx, box, species, x, u, id, n);
 }
 
-// Fields to the host.  Small boxes (all their fields within kPinnedBytes of the
-// arena, FP32 form up to 8736 cells): one copy into the context's pinned buffer,
-// converted from there, since launches and copies cost more than the values
-// (16^3 cells: 31 us; 54 with a copy and a wait for each field).  Larger ones: the FP32
-// form's are converted on the GPU, in the current's array (zero between steps,
-// and cleared again after its use), and copied from there into the caller's
-// arrays; the FP64 form's are copied as they lie.  (64^3 cells: 2.4 ms, most of
-// it the caller's fresh pages; converted by the host, 3.5.)
+// Fields to the host, through the context's pinned buffer and converted from
+// there.  Small boxes (all their fields within kPinnedBytes of the arena, FP32
+// form up to 8736 cells): one copy, since copies and waits cost more than the
+// values (16^3 cells: 31 us; 54 with a copy and a wait for each field).  Larger
+// ones: each field in parts of half the buffer.  (32^3 cells 126 us, 64^3 0.9
+// ms; copied into pageable memory as they lie and converted then 148 us and 3.1
+// ms, converted by a kernel and copied into the caller's arrays 193 us and 1.4
+// ms.)
 template <typename R>
 static int get_fields_t(pic_ctx *ctx, int box, double *e, double *b, double *j)
 {
     const BoxDev<R> &D = bdvec<R>(ctx)[box];
     const int64_t n3 = 3 * D.nc;
-    double *scratch = reinterpret_cast<double *>(D.J);
     const char *first = reinterpret_cast<const char *>(D.e);       // e, b, bn, J lie in this order
     const size_t span = reinterpret_cast<const char *>(D.J + n3) - first;
     if (span <= kPinnedBytes) {
@@ -1124,29 +1123,29 @@ static int get_fields_t(pic_ctx *ctx, int box, double *e, double *b, double *j)
         out(j, D.J, ctx->fp64 ? 1.0 : std::ldexp(1.0, -kQBits));
         return PIC_OK;
     }
-    auto out = [&](double *to, const double *from) {
-        return hipMemcpyAsync(to, from, n3 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream);
+    // one half of the pinned buffer is filled while the other is converted
+    auto out = [&](double *to, const auto *from, double scale) -> hipError_t {
+        if (!to) return hipSuccess;
+        constexpr size_t half = kPinnedBytes / 2;
+        const int64_t part = half / sizeof(*from);
+        auto fill = [&](int64_t q) {
+            return hipMemcpyAsync(ctx->pinned + q / part % 2 * half, from + q, std::min(part, n3 - q) * sizeof(*from),
+                                  hipMemcpyDeviceToHost, ctx->stream);
+        };
+        hipError_t rc = fill(0);
+        for (int64_t q = 0; rc == hipSuccess && q < n3; q += part) {
+            rc = hipStreamSynchronize(ctx->stream);
+            if (rc == hipSuccess && q + part < n3) rc = fill(q + part);
+            if (rc != hipSuccess) break;
+            const auto *v = reinterpret_cast<decltype(from)>(ctx->pinned + q / part % 2 * half);
+            const int64_t n = std::min(part, n3 - q);
+            for (int64_t i = 0; i < n; ++i) to[q + i] = (double)v[i] * scale;
+        }
+        return rc;
     };
-    if constexpr (sizeof(R) == 8) {
-        if (e) HIPCHK(out(e, D.e));
-        if (b) HIPCHK(out(b, cur_b(ctx, D)));
-        if (j) HIPCHK(out(j, D.J));
-    } else {
-        if (j) {
-            HIPCHK(launch_fields_out(D.J, std::ldexp(1.0, -kQBits), n3, scratch, ctx->stream));   // in place
-            HIPCHK(out(j, scratch));
-        }
-        if (e) {
-            HIPCHK(launch_fields_out(D.e, 1.0, n3, scratch, ctx->stream));
-            HIPCHK(out(e, scratch));
-        }
-        if (b) {
-            HIPCHK(launch_fields_out(cur_b(ctx, D), 1.0, n3, scratch, ctx->stream));
-            HIPCHK(out(b, scratch));
-        }
-        if (e || b || j) HIPCHK(launch_zero(scratch, n3, ctx->stream));
-    }
-    HIPCHK(hipStreamSynchronize(ctx->stream));
+    HIPCHK(out(e, (const R *)D.e, 1.0));
+    HIPCHK(out(b, (const R *)cur_b(ctx, D), 1.0));
+    HIPCHK(out(j, (const typename JType<R>::T *)D.J, ctx->fp64 ? 1.0 : std::ldexp(1.0, -kQBits)));
     return PIC_OK;
 }
 
@@ -1157,14 +1156,31 @@ int pic_get_fields(pic_ctx *ctx, int box, double *e, double *b, double *j)
     return ctx->fp64 ? get_fields_t<double>(ctx, box, e, b, j) : get_fields_t<float>(ctx, box, e, b, j);
 }
 
-// Fields from the host, converted on the GPU through the current's array (zero
-// between steps, and cleared again).
+// Fields from the host.  Where each fits the pinned buffer (periodic boxes of up
+// to 43690 cells, FP64 form 21845): converted into it and copied, both at once
+// where half of it does (16^3 cells: 28 us; 53 by a kernel, 35 through pageable
+// memory).  Else converted on the GPU through the current's array, zero between
+// steps and cleared again (40^3 cells: 150 us; 211 by the host through pageable
+// memory).
 template <typename R>
 static int set_fields_t(pic_ctx *ctx, int box, const double *e, const double *b)
 {
     const BoxDev<R> &D = bdvec<R>(ctx)[box];
     const int64_t n3 = 3 * D.nc;
     double *scratch = reinterpret_cast<double *>(D.J);
+    if (D.wall < 0 && n3 * sizeof(R) <= kPinnedBytes) {
+        const bool both = n3 * sizeof(R) <= kPinnedBytes / 2;
+        auto in = [&](const double *from, R *to, size_t at) {
+            R *v = reinterpret_cast<R *>(ctx->pinned + at);
+            for (int64_t q = 0; q < n3; ++q) v[q] = (R)from[q];
+            return hipMemcpyAsync(to, v, n3 * sizeof(R), hipMemcpyHostToDevice, ctx->stream);
+        };
+        if (e) HIPCHK(in(e, D.e, 0));
+        if (e && b && !both) HIPCHK(hipStreamSynchronize(ctx->stream));
+        if (b) HIPCHK(in(b, cur_b(ctx, D), both ? kPinnedBytes / 2 : 0));
+        HIPCHK(hipStreamSynchronize(ctx->stream));
+        return PIC_OK;
+    }
     auto in = [&](const double *from, R *to, int is_b) -> hipError_t {
         const hipError_t rc = hipMemcpyAsync(scratch, from, n3 * sizeof(double), hipMemcpyHostToDevice, ctx->stream);
         return rc != hipSuccess ? rc : launch_fields_in<R>(scratch, D.n, D.wall, is_b, to, ctx->stream);

@@ -376,7 +376,6 @@ template <typename R>
 hipError_t launch_diag(const BoxDev<R> *boxes, int box, int64_t nc, const Item *items, int nitems,
                        const StepConst<R> &C, const DiagBuf &out, int hist_len, hipStream_t st);
 // copies to and from the host (pic_io.hip)
-template <typename SRC> hipError_t launch_fields_out(const SRC *src, double scale, int64_t n, double *dst, hipStream_t st);
 template <typename R>
 hipError_t launch_fields_in(const double *src, const int n[3], int wall, int is_b, R *dst, hipStream_t st);
 template <typename R>

@@ -1,5 +1,5 @@
-// gfx950 kernels behind the host copies of pic.h: fields and particles are
-// converted to and from the caller's FP64 layout, and particles put in order,
+// gfx950 kernels behind the host copies of pic.h: particles are converted to and
+// from the caller's FP64 layout and put in order, and fields converted from it,
 // on the GPU, so that a copy carries exactly what the caller's arrays hold and
 // the host touches every value once.
 #include <hip/hip_runtime.h>
@@ -9,14 +9,6 @@
 namespace pic {
 
 // ------------------------------------------------------------------ fields
-
-// n values of a field as FP64; SRC: R, or the current's int64 fixed point
-template <typename SRC>
-__global__ void __launch_bounds__(kBlock) fields_out_kernel(const SRC *src, double scale, int64_t n, double *dst)
-{
-    for (int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x; q < n; q += (int64_t)gridDim.x * kBlock)
-        dst[q] = (double)src[q] * scale;
-}
 
 // A field from FP64; on a wall plane (index 0 along the wall axis) the
 // components that the conductor forbids become zero: tangential e, normal b
@@ -38,13 +30,6 @@ __global__ void __launch_bounds__(kBlock) fields_in_kernel(const double *__restr
 }
 
 static unsigned grid_for(int64_t n) { return (unsigned)(n < (int64_t)2048 * kBlock ? (n + kBlock - 1) / kBlock : 2048); }
-
-template <typename SRC>
-hipError_t launch_fields_out(const SRC *src, double scale, int64_t n, double *dst, hipStream_t st)
-{
-    hipLaunchKernelGGL(fields_out_kernel<SRC>, dim3(grid_for(n)), dim3(kBlock), 0, st, src, scale, n, dst);
-    return hipGetLastError();
-}
 
 template <typename R>
 hipError_t launch_fields_in(const double *src, const int n[3], int wall, int is_b, R *dst, hipStream_t st)
@@ -209,8 +194,6 @@ hipError_t launch_particles_in(const BoxDev<R> *boxes, int box, int s, int lo, i
     return hipGetLastError();
 }
 
-template hipError_t launch_fields_out<float>(const float *, double, int64_t, double *, hipStream_t);
-template hipError_t launch_fields_out<long long>(const long long *, double, int64_t, double *, hipStream_t);
 #define PIC_INSTANTIATE_IO(R)                                                                                         \
     template hipError_t launch_fields_in<R>(const double *, const int[3], int, int, R *, hipStream_t);               \
     template hipError_t launch_particle_offsets<R>(const BoxDev<R> *, int, int, int, int32_t *, hipStream_t);        \

@@ -79,3 +79,20 @@ def test_fields_come_back_as_stored_and_leave_no_current(wall, fp64):
     ge, gb, _ = s.fields(0)
     assert not ge.any() and not gb.any()
     s.close()
+
+
+@pytest.mark.parametrize("fp64", [False, True])
+@pytest.mark.parametrize("dims", [(16, 16, 34), (32, 22, 31), (31, 30, 47)], ids=["one_part", "just_over", "parts_and_rest"])
+def test_fields_come_back_in_parts(dims, fp64):
+    # parts of 65536 FP32 or 32768 FP64 values: 26112, 65472 and 131130 values
+    # per field; what a field holds comes back exactly, and reading it changes
+    # nothing (the second read)
+    n = int(np.prod(dims))
+    rng = np.random.default_rng(n)
+    e, b = (rng.standard_normal(3 * n).astype(np.float32).astype(np.float64) for _ in range(2))
+    s = G.sim(dims, 10.0, 2.0, [64, 64], fp64=fp64)
+    s.set_fields(0, e, b)
+    for _ in range(2):
+        e1, b1, j1 = s.fields(0)
+        assert np.array_equal(np.ravel(e1), e) and np.array_equal(np.ravel(b1), b) and not np.any(j1)
+    s.close()
