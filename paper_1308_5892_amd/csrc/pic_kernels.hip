@@ -2430,12 +2430,21 @@ __global__ void __launch_bounds__(kBlock) diag_particles_kernel(const BoxDev<R> 
                 atomicAdd(reinterpret_cast<unsigned long long *>(&out.hist[q]), (unsigned long long)shist[q]);
 }
 
+// Largest of values that are not negative, by their bits: NaN is above infinity
+// and stays.
+__device__ inline double max_pos(double a, double b)
+{
+    return __longlong_as_double(max(__double_as_longlong(a), __double_as_longlong(b)));
+}
 __device__ inline void atomic_max_pos(double *p, double v)
 {
     atomicMax(reinterpret_cast<unsigned long long *>(p), (unsigned long long)__double_as_longlong(v));
 }
 
 // Field energies (e^t, b^t) and the Gauss-law residual div e - rho at the nodes.
+// The largest residual passes over a node where it is NaN (the sum of squares,
+// NaN then, tells), but is NaN itself where all 64 nodes of a wave are: a field
+// that is NaN throughout does not look like one that obeys Gauss's law.
 // A few blocks stride over the cells, so that the sums' atomics stay few (one
 // block per 256 cells: 0.14 ms on 64^3 cells and 1.03 ms on 796 x 632 x 4).
 constexpr int kDiagFieldBlocks = 1024;
@@ -2464,7 +2473,8 @@ __global__ void __launch_bounds__(kBlock) diag_fields_kernel(const BoxDev<R> *__
         const bool on_wall = B.wall >= 0 && (B.wall == 0 ? i : (B.wall == 1 ? j : k)) == 0;
         const double r = on_wall ? 0.0 : div - rho;   // a wall plane carries the conductor's surface charge
         v[7] += r * r;
-        v[6] = fmax(v[6], fabs(r));
+        const bool nan = r != r, keep = __ballot(nan) == ~0ull;
+        v[6] = max_pos(v[6], nan && !keep ? 0.0 : fabs(r));
     }
     const int wave = threadIdx.x >> 6;
 #pragma unroll
@@ -2472,7 +2482,7 @@ __global__ void __launch_bounds__(kBlock) diag_fields_kernel(const BoxDev<R> *__
         double t = v[q];
         for (int off = 32; off > 0; off >>= 1) {
             const double o = __shfl_down(t, off);
-            t = q == 6 ? fmax(t, o) : t + o;
+            t = q == 6 ? max_pos(t, o) : t + o;
         }
         if (__lane_id() == 0) red[wave][q] = t;
     }
@@ -2480,7 +2490,7 @@ __global__ void __launch_bounds__(kBlock) diag_fields_kernel(const BoxDev<R> *__
     if (threadIdx.x < 8) {
         const int q = threadIdx.x;
         double t = red[0][q];
-        for (int w = 1; w < kBlock / 64; ++w) t = q == 6 ? fmax(t, red[w][q]) : t + red[w][q];
+        for (int w = 1; w < kBlock / 64; ++w) t = q == 6 ? max_pos(t, red[w][q]) : t + red[w][q];
         double *dst = (double *)(out.copy(blockIdx.x) + kAccField + q);
         if (q == 6) atomic_max_pos(dst, t);
         else atomicAdd(dst, t);
@@ -2498,7 +2508,7 @@ __global__ void __launch_bounds__(64) diag_collect_kernel(const BoxDev<R> *__res
     const int q = threadIdx.x;
     if (q < kAccLen) {
         double t = out.acc[q];
-        for (int r = 1; r < out.copies; ++r) t = q == kAccField + 6 ? fmax(t, out.copy(r)[q]) : t + out.copy(r)[q];
+        for (int r = 1; r < out.copies; ++r) t = q == kAccField + 6 ? max_pos(t, out.copy(r)[q]) : t + out.copy(r)[q];
         out.acc[q] = t;
     }
     if (q < kMaxSpecies) out.rho[q] = q < C.nsp ? (double)B.sp[q].nb[C.cur][B.ntiles] : 0.0;
