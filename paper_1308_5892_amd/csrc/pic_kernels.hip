@@ -1105,8 +1105,12 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
     const int tid = threadIdx.x;
     const TileGeom<R> g = tile_geom<R, FIX>(B, T);
     const TileRim rim = tile_rim(B, g);
-    // 4x4x4 tiles take the packed loop, except those on a conducting wall
-    bool packed = FIX != 0;
+    // 4x4x4 tiles take the packed loop, except those on a conducting wall and
+    // the FP64 form with walls, whose 168 registers do not hold both loops: with
+    // the packed one in it the kernel had 272 B of scratch per lane and took 390
+    // us on 64^3 cells with 16 pairs per cell, with the general loop alone 292
+    constexpr bool kPacked = FIX != 0 && !(WALLS != 0 && sizeof(R) == 8);
+    bool packed = kPacked;
     if (WALLS) {
 #pragma unroll
         for (int a = 0; a < 3; ++a) packed = packed && !(B.wall == a && (g.o[a] == 0 || g.o[a] + g.ext[a] == B.n[a]));
@@ -1430,7 +1434,7 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
             pb = npb;
         }
     };
-    if constexpr (FIX != 0) {
+    if constexpr (kPacked) {
         if (packed) packed_loop();
     }
     // the general loop: other tile shapes, tiles on a conducting wall
@@ -1683,7 +1687,7 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
                 const PBuf<R> &Q = sh_q[s];
                 const int from = q + sh_loff[s];
                 const PSlot<R> ps = slot_at<FIX != 0>(Q, from);
-                if (FIX && (!WALLS || packed)) hcell[h] = ps.code();
+                if (kPacked && (!WALLS || packed)) hcell[h] = ps.code();
                 else hcell[h] = slot_ref(Q.cell, from);
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
@@ -1735,7 +1739,7 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
             if (s < 0) continue;
             // the same bin as at staging, and the code in the new tile
             int k, code;
-            if (FIX && (!WALLS || packed)) {
+            if (kPacked && (!WALLS || packed)) {
                 uint32_t t, q;
                 mv.to(leaver_cell((uint32_t)hcell[h]), t, q);
                 k = (int)udot4(t, 0x090301u);
@@ -1751,7 +1755,7 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
             if (!wide) {
                 at = sh_tseg[s][k] + pos;
             } else {                                    // the target segment is full: overflow region
-                if (FIX && (!WALLS || packed)) {        // its particles keep the packed cell
+                if (kPacked && (!WALLS || packed)) {        // its particles keep the packed cell
                     int o[3];
                     tile_origin(B, neighbor_tile(B, g, k), o);
                     hcell[h] = pack_cell(o[0] + (code & 3), o[1] + ((code >> 2) & 3), o[2] + (code >> 4));
