@@ -1168,26 +1168,54 @@ int pic_get_fields(pic_ctx *ctx, int box, double *e, double *b, double *j)
 
 // Fields from the host.  Where each fits the pinned buffer (periodic boxes of up
 // to 43690 cells, FP64 form 21845): converted into it and copied, both at once
-// where half of it does (16^3 cells: 28 us; 53 by a kernel, 35 through pageable
-// memory).  Else converted on the GPU through the current's array, zero between
-// steps and cleared again (40^3 cells: 150 us; 211 by the host through pageable
-// memory).
+// where half of it does (16^3 cells: 21 us; 22 through pageable memory).  Larger
+// periodic boxes: in the FP32 form in equal parts of at most half the buffer, one
+// converted while the one before is copied (e and b of 36^3 cells 72 us, 75
+// through pageable memory, 115 converted by a kernel; 64^3 303, 383 and 370); the
+// FP64 form copies them as they are (28^3 cells 44 us; 64 through a copy on the
+// host, 67 through a kernel).  Boxes with walls: converted on the GPU through the
+// current's array, zero between steps and cleared again.
 template <typename R>
 static int set_fields_t(pic_ctx *ctx, int box, const double *e, const double *b)
 {
     const BoxDev<R> &D = bdvec<R>(ctx)[box];
     const int64_t n3 = 3 * D.nc;
     double *scratch = reinterpret_cast<double *>(D.J);
+    constexpr size_t half = kPinnedBytes / 2;
+    auto convert = [](const double *from, char *to, int64_t n) {
+        R *v = reinterpret_cast<R *>(to);
+        for (int64_t q = 0; q < n; ++q) v[q] = (R)from[q];
+    };
     if (D.wall < 0 && n3 * sizeof(R) <= kPinnedBytes) {
-        const bool both = n3 * sizeof(R) <= kPinnedBytes / 2;
+        const bool both = n3 * sizeof(R) <= half;
         auto in = [&](const double *from, R *to, size_t at) {
-            R *v = reinterpret_cast<R *>(ctx->pinned + at);
-            for (int64_t q = 0; q < n3; ++q) v[q] = (R)from[q];
-            return hipMemcpyAsync(to, v, n3 * sizeof(R), hipMemcpyHostToDevice, ctx->stream);
+            convert(from, ctx->pinned + at, n3);
+            return hipMemcpyAsync(to, ctx->pinned + at, n3 * sizeof(R), hipMemcpyHostToDevice, ctx->stream);
         };
         if (e) HIPCHK(in(e, D.e, 0));
         if (e && b && !both) HIPCHK(hipStreamSynchronize(ctx->stream));
-        if (b) HIPCHK(in(b, cur_b(ctx, D), both ? kPinnedBytes / 2 : 0));
+        if (b) HIPCHK(in(b, cur_b(ctx, D), both ? half : 0));
+        HIPCHK(hipStreamSynchronize(ctx->stream));
+        return PIC_OK;
+    }
+    if (D.wall < 0) {
+        const int64_t parts = (n3 * (int64_t)sizeof(R) + half - 1) / half, part = (n3 + parts - 1) / parts;
+        size_t at = 0;
+        auto in = [&](const double *from, R *to) -> hipError_t {
+            if (sizeof(R) == sizeof(double))
+                return hipMemcpyAsync(to, from, n3 * sizeof(double), hipMemcpyHostToDevice, ctx->stream);
+            hipError_t rc = hipSuccess;
+            for (int64_t q = 0; rc == hipSuccess && q < n3; q += part, at ^= half) {
+                const int64_t n = std::min(part, n3 - q);
+                convert(from + q, ctx->pinned + at, n);
+                rc = hipStreamSynchronize(ctx->stream);       // the other half's copy, and so its next use
+                if (rc == hipSuccess)
+                    rc = hipMemcpyAsync(to + q, ctx->pinned + at, n * sizeof(R), hipMemcpyHostToDevice, ctx->stream);
+            }
+            return rc;
+        };
+        if (e) HIPCHK(in(e, D.e));
+        if (b) HIPCHK(in(b, cur_b(ctx, D)));
         HIPCHK(hipStreamSynchronize(ctx->stream));
         return PIC_OK;
     }

@@ -10,22 +10,18 @@ namespace pic {
 
 // ------------------------------------------------------------------ fields
 
-// A field from FP64; on a wall plane (index 0 along the wall axis) the
-// components that the conductor forbids become zero: tangential e, normal b
-// (App. A.4).
+// A field of a box with walls from FP64: on the wall plane (index 0 along the
+// wall axis) the components that the conductor forbids become zero, tangential e
+// and normal b (App. A.4).
 template <typename R>
 __global__ void __launch_bounds__(kBlock) fields_in_kernel(const double *__restrict__ src, int n0, int n1, int64_t nc,
                                                            int wall, int is_b, R *__restrict__ dst)
 {
     for (int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x; q < 3 * nc; q += (int64_t)gridDim.x * kBlock) {
-        bool zero = false;
-        if (wall >= 0) {
-            const int c = (int)(q / nc);
-            const uint32_t p = (uint32_t)(q - c * nc), r = p / (uint32_t)n0;   // nc <= 2^32
-            const uint32_t i = wall == 0 ? p - r * (uint32_t)n0 : (wall == 1 ? r % (uint32_t)n1 : r / (uint32_t)n1);
-            zero = i == 0 && (is_b ? c == wall : c != wall);
-        }
-        dst[q] = zero ? R(0) : (R)src[q];
+        const int c = (int)(q / nc);
+        const uint32_t p = (uint32_t)(q - c * nc), r = p / (uint32_t)n0;   // nc <= 2^32
+        const uint32_t i = wall == 0 ? p - r * (uint32_t)n0 : (wall == 1 ? r % (uint32_t)n1 : r / (uint32_t)n1);
+        dst[q] = i == 0 && (is_b ? c == wall : c != wall) ? R(0) : (R)src[q];
     }
 }
 
