@@ -2696,7 +2696,7 @@ __device__ inline double field_at(const BoxDev<R> &B, int f, int c, const int x[
 // Scratch: the field, [plane][i2][i1], in the box's charge array, where the
 // result goes at the end; tmp, [plane][i2][m1] complex, and behind it the
 // partial powers in the current's array (3 nc words; the two take at most
-// 3 N2 NP (N1 / 2 + 1)).
+// 3 N2 NP (N1 / 2 + 1)), which the last kernel clears again.
 // (One thread per output that formed b^t anew for every term of its sum took
 // 5.9 + 1.0 ms for 796 x 632 cells and 4 planes, these four kernels 0.35.)
 typedef double Mfma4 __attribute__((ext_vector_type(4)));
@@ -2730,9 +2730,9 @@ __global__ void __launch_bounds__(kBlock) spectrum_field_kernel(const BoxDev<R> 
 
 // tmp[r][m1] = sum_i f[r][i] exp(-2 pi i m1 i / N1) over the rows r of all
 // planes: a block takes 128 rows (32 per wave, so that each twiddle factor read
-// feeds two products) and 16 modes.
-__global__ void __launch_bounds__(kBlock) spectrum_rows_kernel(const double *__restrict__ f, int64_t rows, int N1, int nm,
-                                                               double2 *__restrict__ tmp)
+// feeds two products) and 16 modes; value(r, i) is f[r][i].
+template <typename Value>
+__device__ inline void spectrum_rows(int64_t rows, int N1, int nm, double2 *__restrict__ tmp, Value &&value)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     double2 *w = reinterpret_cast<double2 *>(smem);
@@ -2740,20 +2740,23 @@ __global__ void __launch_bounds__(kBlock) spectrum_rows_kernel(const double *__r
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lo = lane & 15, hi = lane >> 4;
     const int64_t r0 = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * 32;
     const int m0 = blockIdx.y * 16, m = min(m0 + lo, N1 - 1);
-    const double *fa = f + min(r0 + lo, rows - 1) * N1, *fb = f + min(r0 + 16 + lo, rows - 1) * N1;
+    const int64_t ra = min(r0 + lo, rows - 1), rb = min(r0 + 16 + lo, rows - 1);
     Mfma4 re[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}}, im[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
     const int step = (int)((int64_t)4 * m % N1);
     int k = (int)((int64_t)hi * m % N1);                    // (m i) mod N1
-    for (int i = hi; i - hi < N1; i += 4) {
+    auto add = [&](double va, double vb) {
         const double2 t = w[k];
-        const double va = i < N1 ? fa[i] : 0.0, vb = i < N1 ? fb[i] : 0.0;
         re[0] = mfma16(va, t.x, re[0]);
         im[0] = mfma16(va, t.y, im[0]);
         re[1] = mfma16(vb, t.x, re[1]);
         im[1] = mfma16(vb, t.y, im[1]);
         k += step;
         if (k >= N1) k -= N1;
-    }
+    };
+    int i = hi;
+#pragma unroll 4
+    for (; i - hi + 4 <= N1; i += 4) add(value(ra, i), value(rb, i));
+    if (N1 & 3) add(i < N1 ? value(ra, i) : 0.0, i < N1 ? value(rb, i) : 0.0);
     if (m0 + lo >= nm) return;
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -2764,61 +2767,122 @@ __global__ void __launch_bounds__(kBlock) spectrum_rows_kernel(const double *__r
         }
 }
 
+__global__ void __launch_bounds__(kBlock) spectrum_rows_kernel(const double *__restrict__ f, int64_t rows, int N1, int nm,
+                                                               double2 *__restrict__ tmp)
+{
+    spectrum_rows(rows, N1, nm, tmp, [&](int64_t r, int i) { return f[r * N1 + i]; });
+}
+
+// The same straight from the grid, without a pass that writes the field first,
+// for short rows: up to kShortRow[f] values, where that is faster.  One block
+// column takes all modes, so each value is read once, but b^t takes five reads
+// with wrapped indices that only the loads in flight of one row cover (rows of
+// 31: e 8.0 us against 3.4 + 5.8, b 17.6 against 4.1 + 5.7; of 4: b 3.8 against
+// 2.3 + 4.0).
+constexpr int kShortRow[2] = {31, 8};
+template <typename R>
+__global__ void __launch_bounds__(kBlock) spectrum_rows_small_kernel(const BoxDev<R> *__restrict__ boxes, int box, int f,
+                                                                     int c, int a1, int a2, int an, R hdt, int64_t rows,
+                                                                     int nm, double2 *__restrict__ tmp)
+{
+    const BoxDev<R> &B = boxes[box];
+    const int N1 = a1 == 0 ? B.n[0] : B.n[1], N2 = a2 == 1 ? B.n[1] : B.n[2];
+    spectrum_rows(rows, N1, nm, tmp, [&](int64_t r, int i) {
+        const int p = (int)((uint32_t)r / (uint32_t)N2), i2 = (int)((uint32_t)r - (uint32_t)p * (uint32_t)N2);
+        const int x[3] = {a1 == 0 ? i : p, a1 == 1 ? i : (a2 == 1 ? i2 : p), a2 == 2 ? i2 : p};
+        return field_at(B, f, c, x, hdt);
+    });
+}
+
 // part[chunk][m2][m1] = sum over the planes of the chunk of
 // |sum_i tmp[p][i][m1] exp(-2 pi i m2 i / N2)|^2: a wave takes 16 x 16 modes
 // of one chunk of planes (blockIdx.y; few modes leave the chip idle otherwise).
+// SPLIT: the four waves of a block take a quarter of the sum over i each, where
+// there are so few tiles of modes that a wave's chain of products is the time
+// (1 x 1 x 256 cells 8 us, without 22).
+template <bool SPLIT>
 __global__ void __launch_bounds__(kBlock) spectrum_cols_kernel(const double2 *__restrict__ tmp, int N2, int NP, int nm,
                                                                int per, double *__restrict__ part)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     double2 *w = reinterpret_cast<double2 *>(smem);
     twiddle_table(w, N2);
-    const int lane = threadIdx.x & 63, lo = lane & 15, hi = lane >> 4;
-    const int tm = (nm + 15) / 16, tile = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+    constexpr int kW = kBlock / 64;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lo = lane & 15, hi = lane >> 4;
+    const int tm = (nm + 15) / 16, tile = SPLIT ? blockIdx.x : blockIdx.x * kW + wave;
     if (tile >= tm * ((N2 + 15) / 16)) return;
     const int m1 = tile % tm * 16 + lo, a0 = tile / tm * 16, m2 = min(a0 + lo, N2 - 1), mc = min(m1, nm - 1);
-    const int step = (int)((int64_t)4 * m2 % N2), k0 = (int)((int64_t)hi * m2 % N2);
+    // groups of four i: all, or this wave's quarter
+    const int groups = (N2 + 3) / 4, g0 = SPLIT ? groups * wave / kW : 0, g1 = SPLIT ? groups * (wave + 1) / kW : groups;
+    const int step = (int)((int64_t)4 * m2 % N2), k0 = (int)((int64_t)(4 * g0 + hi) * m2 % N2);
+    double2 *sum = w + N2;                                  // SPLIT: [wave][q][lane], after the twiddle factors
     double pw[4] = {0.0, 0.0, 0.0, 0.0};
     const int p1 = min(NP, (int)(blockIdx.y + 1) * per);
     for (int p = blockIdx.y * per; p < p1; ++p) {
         const double2 *src = tmp + (int64_t)p * N2 * nm + mc;
         Mfma4 re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
         int k = k0;
-        for (int i = hi; i - hi < N2; i += 4) {
+        auto add = [&](double2 v) {
             const double2 t = w[k];
-            const double2 v = i < N2 ? src[(int64_t)i * nm] : make_double2(0.0, 0.0);
             re = mfma16(t.x, v.x, re);
             im = mfma16(t.x, v.y, im);
             re = mfma16(-t.y, v.y, re);
             im = mfma16(t.y, v.x, im);
             k += step;
             if (k >= N2) k -= N2;
-        }
+        };
+        int i = 4 * g0 + hi;
+        const int full = min(4 * g1, N2 & ~3);
+#pragma unroll 4
+        for (; i - hi < full; i += 4) add(src[(int64_t)i * nm]);
+        if (i - hi < 4 * g1) add(i < N2 ? src[(int64_t)i * nm] : make_double2(0.0, 0.0));
+        if (SPLIT) {
+            // wave q adds up the quarters of the rows hi + 4 q
 #pragma unroll
-        for (int q = 0; q < 4; ++q) pw[q] += re[q] * re[q] + im[q] * im[q];
+            for (int q = 0; q < 4; ++q) sum[(wave * 4 + q) * 64 + lane] = make_double2(re[q], im[q]);
+            __syncthreads();
+            double x = 0.0, y = 0.0;
+#pragma unroll
+            for (int v = 0; v < kW; ++v) {
+                const double2 z = sum[(v * 4 + wave) * 64 + lane];
+                x += z.x;
+                y += z.y;
+            }
+            pw[0] += x * x + y * y;
+            __syncthreads();
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) pw[q] += re[q] * re[q] + im[q] * im[q];
+        }
     }
     if (m1 >= nm) return;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int r = a0 + hi + 4 * q;
+    for (int q = 0; q < (SPLIT ? 1 : 4); ++q) {
+        const int r = a0 + hi + 4 * (SPLIT ? wave : q);
         if (r < N2) part[((int64_t)blockIdx.y * N2 + r) * nm + m1] = pw[q];
     }
 }
+static_assert(kBlock / 64 == 4, "a wave of a split block takes the rows of one register of the product");
 
-// ps[m1 + N1 m2]: the chunks added in order, the modes above N1 / 2 by symmetry.
-__global__ void __launch_bounds__(kBlock) spectrum_sum_kernel(const double *__restrict__ part, int N1, int N2, int nm,
-                                                              int chunks, double *__restrict__ ps)
+// ps[m1 + N1 m2]: the chunks added in order, the modes above N1 / 2 by symmetry;
+// every word of the scratch is cleared, a partial power by the one thread that
+// reads it.
+__global__ void __launch_bounds__(kBlock) spectrum_sum_kernel(double2 *__restrict__ tmp, int64_t ntmp,
+                                                              double *__restrict__ part, int N1, int N2, int nm, int chunks,
+                                                              double *__restrict__ ps)
 {
-    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (t >= (int64_t)N1 * N2) return;
-    int m1 = (int)(t % N1), m2 = (int)(t / N1);
-    if (m1 >= nm) {
-        m1 = N1 - m1;
-        m2 = m2 ? N2 - m2 : 0;
+    const int64_t first = (int64_t)blockIdx.x * kBlock + threadIdx.x, stride = (int64_t)gridDim.x * kBlock;
+    const int64_t modes = (int64_t)N2 * nm;
+    for (int64_t t = first; t < modes; t += stride) {
+        const int m1 = (int)(t % nm), m2 = (int)(t / nm);
+        double v = 0.0;
+#pragma unroll 8
+        for (int c = 0; c < chunks; ++c) v += part[c * modes + t];
+        for (int c = 0; c < chunks; ++c) part[c * modes + t] = 0.0;
+        ps[m1 + (int64_t)N1 * m2] = v;
+        if (m1 > 0 && N1 - m1 >= nm) ps[N1 - m1 + (int64_t)N1 * (m2 ? N2 - m2 : 0)] = v;
     }
-    double v = 0.0;
-    for (int c = 0; c < chunks; ++c) v += part[((int64_t)c * N2 + m2) * nm + m1];
-    ps[t] = v;
+    for (int64_t t = first; t < ntmp; t += stride) tmp[t] = make_double2(0.0, 0.0);
 }
 
 template <typename R>
@@ -2827,23 +2891,37 @@ hipError_t launch_spectrum(const BoxDev<R> *boxes, int box, const int n[3], int 
 {
     const int a1 = an == 0 ? 1 : 0, a2 = an == 2 ? 1 : 2;
     const int N1 = n[a1], N2 = n[a2], NP = n[an], nm = N1 / 2 + 1;
-    const int64_t nc = (int64_t)N1 * N2 * NP, rows = (int64_t)N2 * NP, cols = (int64_t)N1 * N2;
+    const int64_t nc = (int64_t)N1 * N2 * NP, rows = (int64_t)N2 * NP;
     double *field = ps;
     double2 *tmp = reinterpret_cast<double2 *>(scratch);
     const auto blocks = [](int64_t work) { return dim3((unsigned)((work + kBlock - 1) / kBlock)); };
-    hipLaunchKernelGGL(spectrum_field_kernel<R>, blocks(nc), dim3(kBlock), 0, st, boxes, box, f, c, a1, a2, an, hdt, field);
-    hipLaunchKernelGGL(spectrum_rows_kernel, dim3((unsigned)((rows + 127) / 128), (nm + 15) / 16), dim3(kBlock),
-                       N1 * sizeof(double2), st, (const double *)field, rows, N1, nm, tmp);
+    const dim3 rgrid((unsigned)((rows + 127) / 128), (nm + 15) / 16);
+    if (N1 <= kShortRow[f]) {
+        hipLaunchKernelGGL(spectrum_rows_small_kernel<R>, rgrid, dim3(kBlock), N1 * sizeof(double2), st, boxes, box, f, c, a1,
+                           a2, an, hdt, rows, nm, tmp);
+    } else {
+        hipLaunchKernelGGL(spectrum_field_kernel<R>, blocks(nc), dim3(kBlock), 0, st, boxes, box, f, c, a1, a2, an, hdt,
+                           field);
+        hipLaunchKernelGGL(spectrum_rows_kernel, rgrid, dim3(kBlock), N1 * sizeof(double2), st, (const double *)field, rows,
+                           N1, nm, tmp);
+    }
     // the planes in chunks, so that about 2048 waves run
     const int tiles = (nm + 15) / 16 * ((N2 + 15) / 16);
     const int chunks0 = std::min(NP, std::max(1, 2048 / tiles)), per = (NP + chunks0 - 1) / chunks0;
     const int chunks = (NP + per - 1) / per;
     double *part = scratch + 2 * rows * nm;
-    hipLaunchKernelGGL(spectrum_cols_kernel, dim3((tiles + kBlock / 64 - 1) / (kBlock / 64), chunks), dim3(kBlock),
-                       N2 * sizeof(double2), st, (const double2 *)tmp, N2, NP, nm, per, part);
-    hipLaunchKernelGGL(spectrum_sum_kernel, blocks(cols), dim3(kBlock), 0, st, (const double *)part, N1, N2, nm, chunks, ps);
-    // the scratch is the current buffer of the box, which the next push expects cleared
-    hipLaunchKernelGGL(zero_words_kernel, dim3(1024), dim3(kBlock), 0, st, (uint64_t *)scratch, 3 * nc);
+    // split blocks where there is less than a wave per SIMD otherwise and the
+    // quarters are longer than the adding up (four products)
+    if ((int64_t)tiles * chunks <= 1024 && N2 >= 64)
+        hipLaunchKernelGGL(spectrum_cols_kernel<true>, dim3(tiles, chunks), dim3(kBlock),
+                           (N2 + 4 * kBlock) * sizeof(double2), st, (const double2 *)tmp, N2, NP, nm, per, part);
+    else
+        hipLaunchKernelGGL(spectrum_cols_kernel<false>, dim3((tiles + kBlock / 64 - 1) / (kBlock / 64), chunks), dim3(kBlock),
+                           N2 * sizeof(double2), st, (const double2 *)tmp, N2, NP, nm, per, part);
+    // the scratch is the current of the box, which the next push expects cleared
+    const int64_t work = std::max(rows * nm, (int64_t)N2 * nm);
+    hipLaunchKernelGGL(spectrum_sum_kernel, blocks(std::min<int64_t>(work, 1024 * kBlock)), dim3(kBlock), 0, st, tmp, rows * nm,
+                       part, N1, N2, nm, chunks, ps);
     return hipGetLastError();
 }
 
