@@ -401,19 +401,23 @@ static void push_order(const pic_ctx *ctx, const std::vector<Item> &items, std::
         density[b] = np / (double)ctx->bh[b].nc;
         per_tile[b] = np / ctx->bh[b].ntiles + kTileCost;
     }
-    auto cost = [&](const Item &it) {
-        if (it.tile < 0) return 0.0;
-        const BoxHost &H = ctx->bh[it.box];
-        int t = it.tile, cells = 1;
-        for (int a = 0; a < 3; ++a) {
-            const int nt = (H.cfg.n[a] + H.tile[a] - 1) / H.tile[a], i = t % nt;
-            t /= nt;
-            cells *= std::min(H.tile[a], H.cfg.n[a] - i * H.tile[a]);
-        }
-        return density[it.box] * cells + kTileCost;
-    };
+    // cost of every item, in item order (a box's tiles, x fastest, then its
+    // sweeps, which cost nothing), formed once and without divisions (32768
+    // tiles: pic_init 0.52 ms; 0.95 with the cost formed from the tile's number
+    // where it is needed)
+    std::vector<double> cost(n, 0.0);
     double total = 0;
-    for (const Item &it : items) total += cost(it);
+    int at = 0;
+    for (int b = 0; b < ctx->cfg.n_boxes; ++b) {
+        const BoxHost &H = ctx->bh[b];
+        for (int z = 0; z < H.cfg.n[2]; z += H.tile[2])
+            for (int y = 0; y < H.cfg.n[1]; y += H.tile[1]) {
+                const int yz = std::min(H.tile[1], H.cfg.n[1] - y) * std::min(H.tile[2], H.cfg.n[2] - z);
+                for (int x = 0; x < H.cfg.n[0]; x += H.tile[0])
+                    total += cost[at++] = density[b] * (yz * std::min(H.tile[0], H.cfg.n[0] - x)) + kTileCost;
+            }
+        at += kOvfBlocks;
+    }
     // runs: [cut[x], cut[x+1]); a cut goes after the tile that reaches x/X of
     // the total, and after that box's sweeps when the tile is the box's last
     std::vector<int> cut(X + 1, n);
@@ -421,7 +425,7 @@ static void push_order(const pic_ctx *ctx, const std::vector<Item> &items, std::
     double acc = 0;
     for (int i = 0, x = 1; i < n && x < X; ++i) {
         if (items[i].tile < 0) continue;
-        acc += cost(items[i]);
+        acc += cost[i];
         if (acc >= total * x / X) {
             int j = i + 1;
             while (j < n && items[j].tile < 0 && items[j].box == items[i].box) ++j;
@@ -442,11 +446,12 @@ static void push_order(const pic_ctx *ctx, const std::vector<Item> &items, std::
         std::stable_sort(parts.begin(), parts.end(), [&](const std::pair<int, int> &a, const std::pair<int, int> &b) {
             return per_tile[items[a.first].box] > per_tile[items[b.first].box];
         });
+        run[x].reserve(cut[x + 1] - cut[x]);
         for (auto &pr : parts) {
-            for (int i = pr.first; i < pr.second; ++i)
-                if (items[i].tile < 0) run[x].push_back(items[i]);
-            for (int i = pr.first; i < pr.second; ++i)
-                if (items[i].tile >= 0) run[x].push_back(items[i]);
+            int sweeps = pr.second;
+            while (sweeps > pr.first && items[sweeps - 1].tile < 0) --sweeps;
+            run[x].insert(run[x].end(), items.begin() + sweeps, items.begin() + pr.second);
+            run[x].insert(run[x].end(), items.begin() + pr.first, items.begin() + sweeps);
         }
         longest = std::max(longest, run[x].size());
     }
