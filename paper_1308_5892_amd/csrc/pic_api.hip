@@ -265,7 +265,7 @@ struct pic_ctx {
     int bpar = 0;                           // which descriptor array holds the current b (Layout::boxes)
     int64_t step = 0;
     size_t lds_bytes = 0;
-    bool fixed444 = false;             // every tile 4x4x4 and every particle copy below 4 GiB: the fixed-shape push kernel
+    int fix = 0;                       // push kernel: 1 every tile 4x4x4 and every particle copy below 4 GiB, 2 every tile 4x4x4, 0 else
     bool walls = false;                // some box has conducting walls
     int wide = 0;                      // few tiles: the push with this many threads per tile
     bool pending = false;
@@ -550,16 +550,15 @@ static int init_t(pic_ctx *ctx)
     HIPCHK(hipMemcpyAsync(ctx->L.cblocks, cbs.data(), cbs.size() * sizeof(CellBlock), hipMemcpyHostToDevice,
                           ctx->stream));
     size_t lds = 0;
-    bool all444 = true;
+    bool all444 = true, narrow = true;
     for (auto &H : ctx->bh) {
         lds = std::max(lds, push_lds_bytes<R>(H.tile[0], H.tile[1], H.tile[2]));
         all444 = all444 && H.tile[0] == 4 && H.tile[1] == 4 && H.tile[2] == 4;
-        // the fixed-shape kernel addresses a copy's groups with 32-bit byte offsets
-        for (int s = 0; s < ctx->cfg.n_species; ++s)
-            all444 = all444 && PBuf<R>::bytes(H.slots[s]) <= UINT32_MAX;
+        // 32-bit byte offsets reach every group of a copy
+        for (int s = 0; s < ctx->cfg.n_species; ++s) narrow = narrow && PBuf<R>::bytes(H.slots[s]) <= UINT32_MAX;
     }
     ctx->lds_bytes = lds;
-    ctx->fixed444 = all444;
+    ctx->fix = all444 ? (narrow ? 1 : 2) : 0;
     ctx->walls = false;
     int ntiles = 0;
     for (auto &H : ctx->bh) {
@@ -567,7 +566,7 @@ static int init_t(pic_ctx *ctx)
         ntiles += std::min(H.ntiles, kWideTiles + 1);
         if (ntiles > kWideTiles) ntiles = kWideTiles + 1;
     }
-    ctx->wide = ctx->fixed444 && !ctx->walls ? wide_threads<R>(ntiles) : 0;
+    ctx->wide = ctx->fix == 1 && !ctx->walls ? wide_threads<R>(ntiles) : 0;
     HIPCHK(hipStreamSynchronize(ctx->stream));
     // initial segment layout: an empty repack
     return merge_t<R>(ctx, true);
@@ -753,7 +752,7 @@ static int step_t(pic_ctx *ctx, int n)
         mark(ctx, 0, true);
         HIPCHK(launch_push<R>(dev_boxes<R>(ctx), ctx->L.items_push, ctx->n_push,
                               ctx->wide ? wide_lds_bytes<R>(ctx->wide) : ctx->lds_bytes, C,
-                              ctx->fixed444 ? 1 : 0, ctx->walls ? 1 : 0, (ctx->cfg.flags & PIC_FARADAY4) ? 1 : 0,
+                              ctx->fix, ctx->walls ? 1 : 0, (ctx->cfg.flags & PIC_FARADAY4) ? 1 : 0,
                               ctx->wide, ctx->stream));
         mark(ctx, 0, false);
         // the push wrote b^{t+dt/2} into the other b buffer: it is the current one now

@@ -362,7 +362,7 @@ template <typename R> size_t push_lds_bytes(int t0, int t1, int t2);
 template <typename R> size_t wide_lds_bytes(int threads);   // of a wide_push_kernel block (4x4x4 tiles)
 template <typename R>
 hipError_t launch_push(const BoxDev<R> *boxes, const Item *items, int nitems, size_t lds, const StepConst<R> &C,
-                       int fixed444, int walls, int faraday4, int wide, hipStream_t st);
+                       int fix, int walls, int faraday4, int wide, hipStream_t st);
 template <typename R>
 hipError_t launch_fields(const BoxDev<R> *boxes, const CellBlock *blocks, int nblocks, R dt, int nsp, int filter,
                          int clear_copy, int nboxes, Watch watch, hipStream_t st);

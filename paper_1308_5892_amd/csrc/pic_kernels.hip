@@ -1087,7 +1087,9 @@ __device__ void push_overflow(const BoxDev<R> &B, int kblk, const StepConst<R> &
     }
 }
 
-// The push of one work item by a block of NT threads.
+// The push of one work item by a block of NT threads.  FIX: 0 tiles of any
+// shape, 1 all tiles 4x4x4 and every particle copy below 4 GiB (32-bit slot
+// addresses), 2 all tiles 4x4x4.
 template <typename R, int FIX, int WALLS, int F4, int NT>
 __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, const Item *__restrict__ items,
                                            const StepConst<R> &C)
@@ -1189,7 +1191,7 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
     R nx_d[3] = {R(0.5), R(0.5), R(0.5)}, nx_u[3] = {R(0), R(0), R(0)};
     auto fetch_particle = [&](const PBuf<R> &P, const TileRanges &src, int q) {
         const int at = src.slot(min(q, src.n - 1));
-        const PSlot<R> ps = slot_at<FIX != 0>(P, at);
+        const PSlot<R> ps = slot_at<FIX == 1>(P, at);
         nx_code = ps.code();
         nx_d[0] = ps.d(0); nx_d[1] = ps.d(1); nx_d[2] = ps.d(2);
         nx_u[0] = ps.u(0); nx_u[1] = ps.u(1); nx_u[2] = ps.u(2);
@@ -1397,7 +1399,7 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
                 const int bb = dst_start + src.n - 1 - __builtin_amdgcn_readlane(claimed, 1);
                 int at = stay ? fb + lane_rank(ms) : bb - lane_rank(ml);
                 at = valid ? at : spare + lane;
-                const PSlot<R> ps = slot_at<true>(Q, at);
+                const PSlot<R> ps = slot_at<FIX == 1>(Q, at);
                 ps.code() = (uint8_t)(stay ? udot4(q, 0x100401u) : leaver_code(Pw));
 #pragma unroll
                 for (int a = 0; a < 3; ++a) ps.d(a) = offset_in_cell(x1[a]);
@@ -1561,7 +1563,7 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
                 const int slot = atomicAdd(&S.nb[dst][tn], 1);
                 at = b_range_slot(B, S, dst, tn, S.bs[dst][tn] + slot, C.flags);
             }
-            if (at >= 0) write_particle<FIX != 0>(S.buf[dst], at, lv || at >= ovf0, ncell, ncode, dn, u, id);
+            if (at >= 0) write_particle<FIX == 1>(S.buf[dst], at, lv || at >= ovf0, ncell, ncode, dn, u, id);
 
             // deposit: the first piece (in the home cell) at once, the move
             // into the wave's queue for its later pieces; the crossings in
@@ -1686,7 +1688,7 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
                 for (int r = 0; r + 1 < kMaxSpecies; ++r) s += (r + 1 < C.nsp && q >= sh_lend[r]) ? 1 : 0;
                 const PBuf<R> &Q = sh_q[s];
                 const int from = q + sh_loff[s];
-                const PSlot<R> ps = slot_at<FIX != 0>(Q, from);
+                const PSlot<R> ps = slot_at<FIX == 1>(Q, from);
                 if (kPacked && (!WALLS || packed)) hcell[h] = ps.code();
                 else hcell[h] = slot_ref(Q.cell, from);
 #pragma unroll
@@ -1769,7 +1771,7 @@ __device__ __forceinline__ void push_block(const BoxDev<R> *__restrict__ boxes, 
                     at = S.seg_start[dst][B.ntiles] + o;
                 }
             }
-            if (at >= 0) write_particle<FIX != 0>(sh_q[s], at, wide, hcell[h], code, hd[h], hu[h], hid[h]);
+            if (at >= 0) write_particle<FIX == 1>(sh_q[s], at, wide, hcell[h], code, hd[h], hu[h], hid[h]);
         }
     }
 }
@@ -1783,6 +1785,19 @@ __global__ void __launch_bounds__(kBlock, PushWaves<R>::value) push_kernel(const
                                                                            const Item *__restrict__ items, StepConst<R> C)
 {
     push_block<R, FIX, WALLS, F4, kBlock>(boxes, items, C);
+}
+
+// 4x4x4 tiles and a particle copy of 4 GiB or more (125 M particles of a species
+// at the default headroom, 64 M in the FP64 form): 64-bit slot addresses.
+// 128^3 cells, 64 pairs per cell: 3.86 ms; 4.14 with the kernel for tiles of any
+// shape.  (32-bit addresses, where they reach: 64^3, 64 pairs 480 us, with these
+// 483; FP64 866 and 873.)
+template <typename R, int WALLS, int F4>
+__global__ void __launch_bounds__(kBlock, PushWaves<R>::value) far_push_kernel(const BoxDev<R> *__restrict__ boxes,
+                                                                               const Item *__restrict__ items,
+                                                                               StepConst<R> C)
+{
+    push_block<R, 2, WALLS, F4, kBlock>(boxes, items, C);
 }
 
 // Launches that leave CUs idle take more threads per tile (wide_threads): the
@@ -2528,11 +2543,11 @@ size_t wide_lds_bytes(int threads) { return tile_lds<R>(4, 4, 4, threads / 64).t
 
 template <typename R>
 hipError_t launch_push(const BoxDev<R> *boxes, const Item *items, int nitems, size_t lds, const StepConst<R> &C,
-                       int fixed444, int walls, int faraday4, int wide, hipStream_t st)
+                       int fix, int walls, int faraday4, int wide, hipStream_t st)
 {
     // dynamic LDS beyond 64 KiB has to be allowed per kernel: the limit each
     // variant was last raised to, raised again when a launch needs more
-    static size_t raised[10] = {65536, 65536, 65536, 65536, 65536, 65536, 65536, 65536, 65536, 65536};
+    static size_t raised[13] = {65536, 65536, 65536, 65536, 65536, 65536, 65536, 65536, 65536, 65536, 65536, 65536, 65536};
     auto go = [&](auto kern, int v, int threads = kBlock) -> hipError_t {
         if (lds > raised[v]) {
             const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -2548,9 +2563,13 @@ hipError_t launch_push(const BoxDev<R> *boxes, const Item *items, int nitems, si
     }
     if (wide) return faraday4 ? go(wide_push_kernel<R, 1, 512>, 7, 512) : go(wide_push_kernel<R, 0, 512>, 6, 512);
     // walls and the fourth-order solver are never combined (pic_plan refuses it)
-    if (walls) return fixed444 ? go(push_kernel<R, 1, 1, 0>, 3) : go(push_kernel<R, 0, 1, 0>, 2);
-    if (faraday4) return fixed444 ? go(push_kernel<R, 1, 0, 1>, 5) : go(push_kernel<R, 0, 0, 1>, 4);
-    return fixed444 ? go(push_kernel<R, 1, 0, 0>, 1) : go(push_kernel<R, 0, 0, 0>, 0);
+    if (fix == 2) {
+        if (walls) return go(far_push_kernel<R, 1, 0>, 11);
+        return faraday4 ? go(far_push_kernel<R, 0, 1>, 12) : go(far_push_kernel<R, 0, 0>, 10);
+    }
+    if (walls) return fix ? go(push_kernel<R, 1, 1, 0>, 3) : go(push_kernel<R, 0, 1, 0>, 2);
+    if (faraday4) return fix ? go(push_kernel<R, 1, 0, 1>, 5) : go(push_kernel<R, 0, 0, 1>, 4);
+    return fix ? go(push_kernel<R, 1, 0, 0>, 1) : go(push_kernel<R, 0, 0, 0>, 0);
 }
 
 template <typename R>
