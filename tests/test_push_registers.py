@@ -28,3 +28,22 @@ def test_fp64_push_kernels_keep_their_register_budget(P, tmp_path):  # noqa: F81
         walls = re.match(r"_ZN3pic11push_kernelIdLi\dELi(\d)E", name).group(1) == "1"
         assert m["vgpr_count"] <= 168 and m["vgpr_spill_count"] == 0, (name, m)
         assert m["private_segment_fixed_size"] <= (32 if walls else 0), (name, m)
+
+
+def test_other_push_kernels_keep_the_budgets(P, tmp_path):  # noqa: F811
+    # the variants with 64-bit slots as the plain ones; those with 512 or 1024
+    # threads per tile at most 128 VGPRs (1024 threads are four waves per SIMD);
+    # all within the static LDS that pic_plan keeps back
+    far = _kernels(P.LIB_PATH, tmp_path, "_ZN3pic15far_push_kernel")
+    wide = _kernels(P.LIB_PATH, tmp_path, "_ZN3pic16wide_push_kernel")
+    assert len(far) == 6 and len(wide) == 6
+    for name, m in far.items():
+        form, walls = re.match(r"_ZN3pic15far_push_kernelI([fd])Li(\d)E", name).groups()
+        scratch = 0 if walls == "0" else (16 if form == "f" else 32)
+        assert m["vgpr_count"] <= (128 if form == "f" else 168) and m["vgpr_spill_count"] == 0, (name, m)
+        assert m["private_segment_fixed_size"] <= scratch, (name, m)
+    for name, m in wide.items():
+        assert m["vgpr_count"] <= 128 and m["vgpr_spill_count"] == 0, (name, m)
+        assert m["private_segment_fixed_size"] == 0, (name, m)
+    for name, m in {**far, **wide}.items():
+        assert m["group_segment_fixed_size"] <= 2176, (name, m)
