@@ -167,7 +167,9 @@ typedef struct pic_diag_out {
     double  sum_gm1[PIC_MAX_SPECIES];   /* sum (gamma^t - 1) */
     int64_t n_particles[PIC_MAX_SPECIES];
     int64_t n_overflow[PIC_MAX_SPECIES];   /* particles in the overflow region */
-    double  gauss_max, gauss_rms;       /* |div e - rho| over the nodes, rho = sum alpha_s W(x_p) */
+    double  gauss_max, gauss_rms;       /* |div e - rho| over the nodes, rho = sum alpha_s W(x_p).  A node
+                                           whose residual is NaN makes gauss_rms NaN; gauss_max passes
+                                           over it, unless 64 in a row are */
     uint32_t flags;                     /* PIC_FLAG_* raised since the last report */
 } pic_diag_out;
 
@@ -184,7 +186,9 @@ int pic_plan(const pic_config *cfg, size_t *arena_bytes);
  * (borrowed).  hip_stream: hipStream_t to enqueue on (borrowed; NULL = default).
  * Checks the 3-D Courant bound dt < 1/sqrt(3) (App. B states the bound as
  * dt < X0/sqrt 2, which is the 2-D one) and omega_pe dt = dt/n_x < 2 (App. B),
- * returning PIC_ECOURANT.  Zeroes all fields and particles.
+ * returning PIC_ECOURANT.  The context starts with all fields zero and no
+ * particles.  Besides the arena it takes 512 KiB of pinned host memory, for the
+ * overflow reports of pic_step and for field copies, until pic_free.
  */
 int pic_init(const pic_config *cfg, void *dev_arena, size_t bytes, void *hip_stream,
              pic_ctx **out);
@@ -211,13 +215,13 @@ int pic_set_harris_field(pic_ctx *ctx, const pic_harris_field *h);
  * every sort_interval steps, and also as soon as an overflow region (the
  * slow path for particles whose tile segment is full) is half full, or holds
  * more than 8192 particles:
- * after each push the e update writes the fill of the fullest one into
- * coherent pinned host memory (a few bytes, allocated by pic_init), and
- * pic_step reads that report two steps later, so it keeps the stream at most
- * two steps ahead of the host instead of returning at once.  Which particles take the slow path depends
- * on the order of the slot claims, but it computes the same arithmetic as the
- * tile path, and the FP32 form sums the current in int64 fixed point: a run
- * of the FP32 form is bitwise reproducible.
+ * after each push the e update writes the fill of the fullest one into the
+ * context's pinned host memory, and pic_step waits for that report two steps
+ * later (polling), so it keeps the stream at most two steps ahead of the host
+ * instead of returning at once.  Which particles take the slow path depends on
+ * the order of the slot claims, but it computes the same arithmetic as the tile
+ * path, and the FP32 form sums the current in int64 fixed point: a run of the
+ * FP32 form is bitwise reproducible.
  */
 int pic_step(pic_ctx *ctx, int n);
 

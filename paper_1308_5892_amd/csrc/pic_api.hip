@@ -240,7 +240,7 @@ using namespace pic;
 constexpr int kWatch = 4, kWatchLag = 2;
 constexpr uint32_t kWatchLimit = 500;
 
-// pinned host memory of a context: the watch's slots, then a buffer for small
+// pinned host memory of a context: the watch's slots, then a buffer for field
 // copies
 constexpr size_t kPinnedBytes = 512 * 1024;
 
@@ -378,8 +378,8 @@ static StepConst<R> step_const(pic_ctx *ctx)
 // XCD: blocks go round-robin over the 8 XCDs of the MI355X, so block b runs
 // item (b / 8) of run (b % 8), and a box's neighbouring tiles meet in one L2.
 // A tile costs its share of the box's particles, by its cells, plus a fixed
-// set-up worth kTileCost particles; the cut falls on tile boundaries, so the
-// runs differ by less than one tile.  (With one cost for all tiles of a box,
+// set-up worth kTileCost particles; the cut falls on tile boundaries, so each
+// run is within one (the dearest) tile of the mean.  (With one cost for all tiles of a box,
 // the half of the runs that held the one-cell-thick last layer of a 250 x 198 x
 // 5 box had a quarter of the particles of the others: push 0.92 ms against
 // 0.75.)  Within a run the boxes go in decreasing cost per tile (the
@@ -623,8 +623,9 @@ int pic_init(const pic_config *cfg, void *dev_arena, size_t bytes, void *hip_str
     ctx->binned.assign(cfg->n_boxes, std::vector<int64_t>(kMaxSpecies, 0));
     ctx->stage_half.assign(cfg->n_boxes, std::vector<int32_t>(kMaxSpecies, 0));
     ctx->next_id.assign(cfg->n_boxes, std::vector<int32_t>(kMaxSpecies, 0));
-    // the e update writes the watch straight into these slots (coherent, so
-    // the host reads it once the step's event has completed): no copy per step
+    // the e update writes the watch straight into these slots, with the step's
+    // number, for which the host polls (wait_watch): no copy and no event per
+    // step.  A report that has arrived does not mean that its kernel has ended.
     if (hipHostMalloc(reinterpret_cast<void **>(&ctx->watch_host), 256 + kPinnedBytes, hipHostMallocCoherent) !=
         hipSuccess) {
         ctx->watch_host = nullptr;

@@ -1,7 +1,7 @@
 // Internal device-side layout of the gfx950 PIC library (not part of the ABI).
 //
-// Particles of one (box, species) live in SoA arrays binned by spatial tile.
-// Two copies of the arrays alternate between steps: the push reads copy
+// Particles of one (box, species) live in slots binned by spatial tile (PBuf).
+// Two copies of them alternate between steps: the push reads copy
 // `cur` and writes every particle straight into the segment of its new tile in
 // copy `cur ^ 1`, so the binning is refreshed every step at no extra traffic.
 // Tile T owns the slots [seg_start[c][T], seg_start[c][T] + seg_cap[c][T]) of
@@ -17,8 +17,9 @@
 // (fields read from HBM, current added with global atomics).  A counting-sort
 // repack recomputes the segment layout from the actual counts.
 //
-// Stored particle state: cell packed as ix | iy << 11 | iz << 22, in-cell
-// offset d in [0, 1) per axis, and u = gamma v / c.
+// Stored particle state: the cell (a one-byte code local to the tile, or packed
+// as ix | iy << 11 | iz << 22), in-cell offset d in [0, 1) per axis, and u =
+// gamma v / c.
 #pragma once
 
 #include <hip/hip_runtime.h>

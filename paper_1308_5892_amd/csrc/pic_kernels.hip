@@ -389,9 +389,11 @@ constexpr int kCoef = 48 + 16 / (int)sizeof(R);
 // with planes of 49 (sum over the banks of the square of their load 152 against
 // 160, 16 cells of an x-z plane 16 against 24).  Push with planes of 52
 // against 49: 33.5 M thermal particles 500 against 510 us, in FP64 895 against
-// 916, two beams 570 against 603, Harris sheet 409 against 420.  Planes of 60 are
-// as fast and take more room; rows of 8 with planes of 60 were slower for beams
-// (694 us: the rows of a plane then share banks).
+// 916; over 200 steps after 20, two beams 575 against 606, Harris sheet 411
+// against 422 (over 20 steps after 5, while the clock still falls, 624 against
+// 651 and 442 against 450).  Planes of 60 are as fast and take more room; rows of
+// 8 with planes of 60 were slower for beams (694 us over 20 steps: the rows of a
+// plane then share banks).
 struct CurrentGrid {
     int x, xy, n;
     __host__ __device__ constexpr CurrentGrid(int t0, int t1, int t2)
