@@ -7,6 +7,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <numeric>
 #include <string>
@@ -278,6 +279,10 @@ struct pic_ctx {
     uint64_t *watch_host = nullptr;          // pinned, coherent, kWatch slots
     uint64_t *watch_dev = nullptr;           // the same slots as the device addresses them
     char *pinned = nullptr;                  // kPinnedBytes behind the slots
+    // held by the calls that copy fields or particles: they share the pinned
+    // buffer, and those of particles the counts and the info words, which threads
+    // that read the boxes of one context at the same time would spoil
+    std::mutex copies;
     int64_t last_repack = 0;
     int64_t early_repacks = 0;
     ~pic_ctx()
@@ -1047,6 +1052,7 @@ int pic_get_particles(pic_ctx *ctx, int box, int species, double *x, double *u, 
     int rc = check_box(ctx, box);
     if (rc) return rc;
     if (species < 0 || species >= ctx->cfg.n_species || !n) return PIC_EINVAL;
+    std::lock_guard<std::mutex> hold(ctx->copies);
     rc = merge(ctx);
     if (rc) return rc;
     return ctx->fp64 ? get_particles_t<double>(ctx, box, species, x, u, id, n)
@@ -1091,6 +1097,7 @@ int pic_set_particles(pic_ctx *ctx, int box, int species, const double *x, const
     int rc = check_box(ctx, box);
     if (rc) return rc;
     if (species < 0 || species >= ctx->cfg.n_species || n < 0 || (n > 0 && (!x || !u))) return PIC_EINVAL;
+    std::lock_guard<std::mutex> hold(ctx->copies);
     // other pending loads are binned first so that the flags of a stage stay uniform
     if (ctx->pending) {
         rc = merge(ctx);
@@ -1168,6 +1175,7 @@ int pic_get_fields(pic_ctx *ctx, int box, double *e, double *b, double *j)
 {
     int rc = check_box(ctx, box);
     if (rc) return rc;
+    std::lock_guard<std::mutex> hold(ctx->copies);
     return ctx->fp64 ? get_fields_t<double>(ctx, box, e, b, j) : get_fields_t<float>(ctx, box, e, b, j);
 }
 
@@ -1239,6 +1247,7 @@ int pic_set_fields(pic_ctx *ctx, int box, const double *e, const double *b)
 {
     int rc = check_box(ctx, box);
     if (rc) return rc;
+    std::lock_guard<std::mutex> hold(ctx->copies);
     return ctx->fp64 ? set_fields_t<double>(ctx, box, e, b) : set_fields_t<float>(ctx, box, e, b);
 }
 
