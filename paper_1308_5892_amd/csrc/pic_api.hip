@@ -115,10 +115,6 @@ static size_t carve(Bump &A, const pic_config *cfg, std::vector<BoxHost> &bh, st
     return clear;
 }
 
-// LDS one workgroup may allocate on gfx950 (160 KiB per CU, minus the push
-// kernel's static counters and tables)
-constexpr size_t kMaxLds = 160 * 1024 - 2176;
-
 static int validate(const pic_config *cfg, std::vector<BoxHost> &bh, std::string &err)
 {
     if (!cfg || cfg->n_boxes < 1 || !cfg->boxes) { err = "need at least one box"; return PIC_EINVAL; }

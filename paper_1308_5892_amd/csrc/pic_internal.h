@@ -52,6 +52,9 @@ constexpr int wide_threads(int tiles)
     return tiles > kWideTiles ? 0 : (tiles <= kWideTiles / 2 && sizeof(R) == 4 ? 1024 : 512);
 }
 constexpr int kQBits = 31;         // fractional bits of the fixed-point current
+// LDS one workgroup may allocate on gfx950 (160 KiB per CU, minus the push
+// kernel's static counters and tables)
+constexpr size_t kMaxLds = 160 * 1024 - 2176;
 
 __host__ __device__ inline int32_t pack_cell(int ix, int iy, int iz)
 {

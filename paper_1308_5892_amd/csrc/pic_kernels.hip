@@ -2569,15 +2569,16 @@ template <typename R>
 hipError_t launch_push(const BoxDev<R> *boxes, const Item *items, int nitems, size_t lds, const StepConst<R> &C,
                        int fix, int walls, int faraday4, int wide, hipStream_t st)
 {
-    // dynamic LDS beyond 64 KiB has to be allowed per kernel: the limit each
-    // variant was last raised to, raised again when a launch needs more
+    // dynamic LDS beyond 64 KiB has to be allowed per kernel; where a launch
+    // needs it the limit goes to the largest at once, so that no thread lowers it
+    // for another
     static size_t raised[13] = {65536, 65536, 65536, 65536, 65536, 65536, 65536, 65536, 65536, 65536, 65536, 65536, 65536};
     auto go = [&](auto kern, int v, int threads = kBlock) -> hipError_t {
         if (lds > raised[v]) {
             const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
             if (e != hipSuccess) return e;
-            raised[v] = lds;
+            raised[v] = kMaxLds;
         }
         hipLaunchKernelGGL(kern, dim3(nitems), dim3(threads), lds, st, boxes, items, C);
         return hipGetLastError();
@@ -2636,9 +2637,11 @@ hipError_t launch_repack(const BoxDev<R> *boxes, int nboxes, const Item *items, 
     if (half) {
         // before the binned particles follow the staged ones into the tiles
         auto go = [&](auto kern) -> hipError_t {
+            // the same limit in every call, so that contexts of different tile
+            // shapes in several threads do not lower it for each other
             if (lds > 65536) {
                 const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
                 if (e != hipSuccess) return e;
             }
             hipLaunchKernelGGL(kern, dim3(nitems), dim3(kBlock), lds, st, boxes, items, half, C);

@@ -1,5 +1,6 @@
 """Several threads: boxes of one context copied to and from the host at the same
-time (the library's calls release Python's lock)."""
+time, and contexts loaded at the same time (the library's calls release
+Python's lock)."""
 from concurrent.futures import ThreadPoolExecutor
 
 import numpy as np
@@ -43,3 +44,36 @@ def test_boxes_of_one_context_copied_by_several_threads(fp64):
     with ThreadPoolExecutor(len(dims)) as pool:
         assert list(pool.map(work, range(len(dims)))) == list(range(len(dims)))
     s.close()
+
+
+def test_contexts_loaded_by_several_threads():
+    # tile shapes whose backward half step needs different amounts of LDS, all
+    # above the default limit of 64 KiB; a load's momenta depend on nothing else
+    import torch
+    from paper_1308_5892_amd import pic as P
+    tiles = [(8, 4, 4), (8, 8, 4), (4, 8, 8), (8, 8, 2)]
+    dims, ppc = (16, 16, 8), 2
+    n = ppc * int(np.prod(dims))
+    rng = np.random.default_rng(2)
+    e, b = G.random_fields(rng, int(np.prod(dims)), 0.02, 0.2)
+
+    def load(tile):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            out = []
+            for _ in range(6):
+                s = P.Simulation([{"n": dims, "n_x": 10.0, "rho0": 4.0, "max_particles": [n, n], "tile": tile}], G.PAIR, 0.5,
+                                 fp64=True, track_ids=True)
+                s.set_fields(0, e, b)
+                s.load(0, 0, 1, (0.2, 0.3, 0), (0.2, -0.3, 0), ppc, seed=4)
+                s.step(0)
+                out.append(s.particles(0, 0)[1])
+                s.step(2)
+                s.sync()
+                s.close()
+            return out
+
+    ref = load(tiles[0])[0]
+    with ThreadPoolExecutor(len(tiles)) as pool:
+        for got in pool.map(load, tiles):
+            assert all(np.array_equal(u, got[0]) for u in got)
+            assert np.abs(got[0] - ref).max() <= 1e-13 * np.abs(ref).max()    # the same sums, in FP64
