@@ -2745,7 +2745,7 @@ __device__ inline double field_at(const BoxDev<R> &B, int f, int c, const int x[
 // partial powers in the current's array (3 nc words; the two take at most
 // 3 N2 NP (N1 / 2 + 1)), which the last kernel clears again.
 // (One thread per output that formed b^t anew for every term of its sum took
-// 5.9 + 1.0 ms for 796 x 632 cells and 4 planes, these four kernels 0.35.)
+// 5.9 + 1.0 ms for 796 x 632 cells and 4 planes, these four kernels 0.31.)
 typedef double Mfma4 __attribute__((ext_vector_type(4)));
 __device__ inline Mfma4 mfma16(double a, double b, Mfma4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 
